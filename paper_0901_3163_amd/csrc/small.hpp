@@ -1,4 +1,4 @@
-// Launchers of the one-workgroup FP64 small dense kernels (small.hip).
+// Launchers of the FP64 small dense problems (small.hip).
 #pragma once
 #include "internal.hpp"
 
@@ -26,7 +26,8 @@ void minresdr_cycle(hipStream_t s, int m, int k, double* Tb, double* c, double* 
                     double* lam, double* S, double* rho, double* hth, double* info);
 
 // Galerkin projection solves with H = Y^H A Y (k x k complex Hermitian).
-// proj_setup: E, Z (2k x 2k), lamr (2k), work (4*(k+1) doubles).
+// proj_setup: E, Z (2k x 2k), lamr (2k), work (proj_work(k) doubles).
+size_t proj_work(int k);
 void proj_setup(hipStream_t s, int k, const double2* Hc, double* E, double* Z, double* lamr, double* work);
 // d[r] = H^-1 c[r] for r < nrhs; c, d: [nrhs][k] complex.
 void proj_solve(hipStream_t s, int k, int nrhs, const double* Z, const double* lamr, const double2* c, double2* d);

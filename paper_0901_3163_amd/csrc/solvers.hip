@@ -5,7 +5,7 @@
 //    step applies A, re-orthogonalises against the whole basis by classical
 //    Gram-Schmidt twice (tall-skinny V^H w / w - V c kernels), and writes
 //    alpha_j, beta_j into the projected matrix on the device.  At the end of
-//    a cycle one workgroup solves the small FP64 problem (small.hip), the
+//    a cycle the small FP64 problem is solved on the device (small.hip), the
 //    basis is rebuilt out of place (V Y kernel) and the true residual
 //    ||b - M x||/||b|| is checked: the only host synchronisation per cycle.
 //    Cycles continue past linear convergence to refine the eigenvectors
@@ -702,7 +702,7 @@ dl_eig* eig_build(dl_op* op, int k, DBuf<double2>&& Y, long* mvp) {
   DL_HIP(hipMemcpyAsync(hn.data(), nrm.get(), k * sizeof(double), hipMemcpyDeviceToHost, s));
   e->Zr.alloc(4 * (size_t)k * k);
   e->lamr.alloc(2 * (size_t)k);
-  DBuf<double> E(4 * (size_t)k * k), work(4 * (size_t)(k + 1) + 16);
+  DBuf<double> E(4 * (size_t)k * k), work(proj_work(k));
   {
     TimeScope ts(op->ctx, T_SMALL);
     proj_setup(s, k, Hc.get(), E.get(), e->Zr.get(), e->lamr.get(), work.get());

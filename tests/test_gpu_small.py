@@ -1,0 +1,39 @@
+"""The projected problems of the restarts at the edges of their launch shapes: one or several rows
+per lane (64, 128, 192), matrices that just fit in LDS or do not, odd and even orders."""
+import numpy as np
+import pytest
+
+from lattice_inputs import gaussian_spinor
+from oracle import dirac
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind,m,k", [
+    ("g5m", 9, 1), ("g5m", 63, 20), ("g5m", 64, 21), ("g5m", 127, 20), ("g5m", 128, 64), ("g5m", 139, 30),
+    ("g5m", 140, 30), ("g5m", 192, 40), ("g5m", 210, 199), ("mdagm", 20, 1), ("mdagm", 33, 16), ("mdagm", 64, 20),
+    ("mdagm", 141, 20), ("mdagm", 142, 20), ("mdagm", 143, 40), ("mdagm", 202, 141)])
+def test_first_solve_over_basis_sizes(gpu_ctx, c1_config, kind, m, k):
+    """A restarted first solve converges (FP64 residual by the oracle's matrix), and the kept
+    vectors are orthonormal with the residual norms that the handle reports.  The kappa is off
+    critical, so that small bases converge too.  Residual norms of unit vectors are compared to
+    1e-11, the rounding of the Rayleigh quotient (1e-15 ||A||) over the smallest norm kept apart."""
+    from paper_0901_3163_amd import deflan
+    dims, U, kappa = c1_config["dims"], c1_config["links"], 0.13
+    ora = dirac.WilsonOperator(U, dims, kappa)
+    op = deflan.Operator(gpu_ctx, dims, U, kappa, deflan.DL_G5M if kind == "g5m" else deflan.DL_MDAGM)
+    b = gaussian_spinor(dims, 300 + m)
+    x, eig, st = op.solve_first(b, m, k, 1e-10, max_mvp=20000)
+    assert st["status"] == 0, st
+    r = b.ravel() - ora.M(x.ravel())
+    assert np.linalg.norm(r) <= 1.0001e-10 * np.linalg.norm(b)
+    ev, res = eig.info()
+    Y = eig.vectors().reshape(k, -1)
+    gram = Y.conj() @ Y.T
+    assert np.max(np.abs(gram - np.eye(k))) < 1e-10
+    for i in sorted({0, k // 2, k - 1}):
+        a = ora.g5M(Y[i]) if kind == "g5m" else ora.Mdag(ora.M(Y[i]))
+        assert abs(np.vdot(Y[i], a).real - ev[i]) < 1e-12
+        assert abs(np.linalg.norm(a - ev[i] * Y[i]) - res[i]) < 1e-11
+    eig.close()
+    op.close()
