@@ -111,18 +111,19 @@ int norm2_partials(hipStream_t s, long n, const double2* a, double* part) {
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_sum_partials(const double* __restrict__ part, int nparts, int width, double* __restrict__ out) {
+k_sum_partials(const double* __restrict__ part, int nparts, int width, double* __restrict__ out,
+               double* __restrict__ last) {
   const int col = blockIdx.x;
   double acc = 0.0;
   const double* p = part + (long)col * nparts;
   for (int i = threadIdx.x; i < nparts; i += kBlock) acc += p[i];
   __shared__ double lds[kBlock / 64];
   const double s = block_sum<kBlock>(acc, lds);
-  if (threadIdx.x == 0) out[col] = s;
+  if (threadIdx.x == 0) *(col < width ? out + col : last) = s;
 }
 
-void sum_partials(hipStream_t s, const double* part, int nparts, int width, double* out) {
-  hipLaunchKernelGGL(k_sum_partials, dim3(width), dim3(kBlock), 0, s, part, nparts, width, out);
+void sum_partials(hipStream_t s, const double* part, int nparts, int width, double* out, double* last) {
+  hipLaunchKernelGGL(k_sum_partials, dim3(width + (last ? 1 : 0)), dim3(kBlock), 0, s, part, nparts, width, out, last);
   DL_HIP(hipGetLastError());
 }
 

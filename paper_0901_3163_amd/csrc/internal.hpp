@@ -221,8 +221,9 @@ int nblocks_for(long n);  // partial count used by the streaming reductions for 
 int dot_partials(hipStream_t s, long n, const double2* a, const double2* b, double* part);  // complex, 2 per block
 int norm2_partials(hipStream_t s, long n, const double2* a, double* part);                  // 1 per block
 // Partials are stored column-major: part[col * nparts + block].
-// out[col] = sum_i part[col * nparts + i] (fixed order); grid = width blocks
-void sum_partials(hipStream_t s, const double* part, int nparts, int width, double* out);
+// out[col] = sum_i part[col * nparts + i] (fixed order); grid = width blocks; last (may be NULL):
+// column `width` is summed into *last by the same launch
+void sum_partials(hipStream_t s, const double* part, int nparts, int width, double* out, double* last = nullptr);
 
 void copy(hipStream_t s, long n, const double2* a, double2* b);
 void zero(hipStream_t s, long n, double2* a);

@@ -170,22 +170,33 @@ __global__ void __launch_bounds__(kBlock) k_fin_minres_rot(const double* part, i
   }
 }
 
-// Lanczos step bookkeeping: Tb[j][j] = Re(c1[j] + c2[j]); beta = sqrt(sum) -> Tb[j+1][j]; sc[S_INV] = 1/beta.
+// The end of a Lanczos step: beta = sqrt(sum of the ||w||^2 partials) -> Tb[j+1][j], Tb[j][j] =
+// Re(c1[j] + c2[j]), vn = w / beta (0 at a breakdown); sc[S_INV] = 1/beta.  Every block sums the
+// partials itself (at most 2048, from L2), which is cheaper than a launch that only sums them.
 __global__ void __launch_bounds__(kBlock)
-k_fin_lanczos(const double* part, int np, double* Tb, int m, int j, const double* c1, const double* c2, double* sc,
-              double tiny) {
+k_lanczos_next(long n, const double* __restrict__ part, int np, double* Tb, int m, int j, const double* c1,
+               const double* c2, double* sc, double tiny, const double2* __restrict__ w, double2* __restrict__ vn) {
   __shared__ double lds[kBlock / 64];
+  __shared__ double sh_inv;
   const double ww = fin_sum(part, np, lds);
   if (threadIdx.x == 0) {
     const double beta = sqrt(ww);
-    Tb[(long)j * m + j] = c1[2 * j] + c2[2 * j];
-    Tb[(long)(j + 1) * m + j] = beta;
     const bool brk = !(beta > tiny);
-    sc[S_INV] = brk ? 0.0 : 1.0 / beta;
-    sc[S_NRM] = beta;
-    if (!isfinite(ww)) sc[S_FLAG] = 1.0;
-    else if (brk && sc[S_FLAG] == 0.0) { sc[S_FLAG] = 2.0; sc[S_BRKJ] = (double)j; }
+    const double inv = brk ? 0.0 : 1.0 / beta;
+    sh_inv = inv;
+    if (blockIdx.x == 0) {
+      Tb[(long)j * m + j] = c1[2 * j] + c2[2 * j];
+      Tb[(long)(j + 1) * m + j] = beta;
+      sc[S_INV] = inv;
+      sc[S_NRM] = beta;
+      if (!isfinite(ww)) sc[S_FLAG] = 1.0;
+      else if (brk && sc[S_FLAG] == 0.0) { sc[S_FLAG] = 2.0; sc[S_BRKJ] = (double)j; }
+    }
   }
+  __syncthreads();
+  const double inv = sh_inv;
+  for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock)
+    vn[i] = c_scale(w[i], inv);
 }
 
 // One residual-history point: out = (mvp, scale * sqrt(sc[idx])) or (mvp, scale * |sc[idx]|).
@@ -799,7 +810,7 @@ int solve_first(dl_op* op, const double2* b, double2* x, int m, int k, double to
   // factors either way
   DBuf<double2> xbest(n);
   double best = HUGE_VAL;
-  DBuf<double> dgks(2);  // [0]: second Gram-Schmidt pass needed (1) or not (0); [1]: ||w||^2
+  DBuf<double> wnorm2(1);  // ||w||^2 before a Gram-Schmidt pass
   const bool kept_reorth = o.reorth == DL_REORTH_KEPT;
   const int period = std::max(1, o.reorth_period);
   DBuf<double> work(std::max(landr_work(m), minresdr_work(m)));
@@ -843,36 +854,38 @@ int solve_first(dl_op* op, const double2* b, double2* x, int m, int k, double to
       // Classical Gram-Schmidt against logical vectors [v0, v0 + nv), the second pass only when the
       // first removed more than half of ||w||^2 (the DGKS criterion, eta = 1/sqrt(2); decided on
       // the device, a skipped pass leaves zero coefficients); the coefficients land at cb[v0..]
-      // (k_fin_lanczos takes alpha_j from entry j of c1 + c2).
-      auto cgs2 = [&](int v0, int nv, double* ca, double* cb2) {
+      // (k_lanczos_next takes alpha_j from entry j of c1 + c2).  norm: the last update also leaves
+      // the partials of ||w||^2 in S.part; returns their count.
+      auto cgs2 = [&](int v0, int nv, double* ca, double* cb2, bool norm) {
+        int np = 0;
         for (int pass = 0; pass < 2; ++pass) {
           double* cb = (pass == 0 ? ca : cb2) + 2 * v0;
-          const double* gate = pass == 0 ? nullptr : dgks.get();
+          TskGate gate;
+          if (pass == 1) gate = TskGate{reinterpret_cast<const double2*>(ca + 2 * v0), nv, wnorm2.get()};
           int nb;
           {
             TimeScope ts(ctx, T_TSK_DOTS);
             nb = tsk_dots(s, n, nv, Vb.get(), n, slot_d.get() + v0, w.get(), S.part.get(), gate, pass == 0);
           }
-          sum_partials(s, S.part.get(), nb, 2 * nv, cb);
-          if (pass == 0) sum_partials(s, S.part.get() + (size_t)2 * nv * nb, nb, 1, dgks.get() + 1);
+          sum_partials(s, S.part.get(), nb, 2 * nv, cb, pass == 0 ? wnorm2.get() : nullptr);
           TimeScope ts(ctx, T_TSK_UPDATE);
-          tsk_update(s, n, nv, Vb.get(), n, slot_d.get() + v0, reinterpret_cast<const double2*>(cb), -1.0, w.get(),
-                     gate);
-          if (pass == 0) tsk_dgks_gate(s, cb, nv, dgks.get() + 1, 0.5, dgks.get());
+          np = tsk_update(s, n, nv, Vb.get(), n, slot_d.get() + v0, reinterpret_cast<const double2*>(cb), -1.0, w.get(),
+                          gate, pass == 1 && norm ? S.part.get() : nullptr);
         }
+        return np;
       };
+      int np;
       if (!kept_reorth || j == j0 || j == 0) {
-        cgs2(0, j + 1, c1.get(), c2.get());  // the whole basis (the arrow column after a restart)
+        np = cgs2(0, j + 1, c1.get(), c2.get(), true);  // the whole basis (the arrow column after a restart)
       } else {
         // the paper's policy: the three-term recurrence's two vectors, and every `period` steps
         // the vectors kept at the last restart (coefficients discarded: zero in exact arithmetic)
-        cgs2(j - 1, 2, c1.get(), c2.get());
-        if (j0 > 0 && (j - j0) % period == 0) cgs2(0, j0, c3.get(), c3.get() + 2 * (m + 1));
+        const bool kept = j0 > 0 && (j - j0) % period == 0;
+        np = cgs2(j - 1, 2, c1.get(), c2.get(), !kept);
+        if (kept) np = cgs2(0, j0, c3.get(), c3.get() + 2 * (m + 1), true);
       }
-      const int nb = norm2_partials(s, n, w.get(), S.part.get());
-      hipLaunchKernelGGL(k_fin_lanczos, dim3(1), dim3(kBlock), 0, s, S.part.get(), nb, Tb.get(), m, j, c1.get(),
-                         c2.get(), S.sc.get(), 1e-14 * anorm);
-      hipLaunchKernelGGL(k_scale, dim3(grid_for(n)), dim3(kBlock), 0, s, n, S.sc.get(), (int)S_INV, w.get(), V(j + 1));
+      hipLaunchKernelGGL(k_lanczos_next, dim3(grid_for(n)), dim3(kBlock), 0, s, n, S.part.get(), np, Tb.get(), m, j,
+                         c1.get(), c2.get(), S.sc.get(), 1e-14 * anorm, w.get(), V(j + 1));
       DL_HIP(hipGetLastError());
       if (anorm == 0.0 || (j - j0) % 16 == 15 || j == m - 1) {
         double h[S_COUNT];

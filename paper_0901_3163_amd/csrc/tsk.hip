@@ -18,93 +18,172 @@
 
 namespace dl {
 
-constexpr int kEPT = 8;        // elements of w cached per thread in the dots kernel
 constexpr int kMaxNV = 512;    // basis vectors per call
+constexpr int kDotsNV = 8;     // basis vectors per block of the dots
+
+// Elements of w per thread of the dots: 8, or 2 when 8 would leave fewer blocks per vector group
+// than the card has CUs (at 8^3 x 16, n = 98304, 48 blocks; a pass over 60 vectors took 95 us).
+static int dots_ept(long n) { return (n + kBlock * 8L - 1) / (kBlock * 8L) < 256 ? 2 : 8; }
 
 int tsk_nblocks(long n) {
-  long nb = (n + (long)kBlock * kEPT - 1) / ((long)kBlock * kEPT);
+  const long per = (long)kBlock * dots_ept(n);
+  long nb = (n + per - 1) / per;
   if (nb < 1) nb = 1;
   if (nb > kMaxPartials) fail(DL_E_INVALID, "vector too long for the tall-skinny reduction");
   return (int)nb;
+}
+
+// A basis larger than the 256 MB Infinity Cache is read with non-temporal loads: it cannot stay there
+// until the next pass (1.5 GB at 16^3 x 32 and 60 vectors: dots 290 -> 265 us, update 295 -> 280 us).
+// A smaller one is read normally and stays (96 MB at 8^3 x 16: 10% slower with non-temporal loads).
+static bool streams(long n, int nv) { return (double)n * nv * sizeof(double2) > 256e6; }
+
+typedef double f64x2_ld __attribute__((ext_vector_type(2)));
+template <bool NT>
+__device__ __forceinline__ double2 ld_vec(const double2* p) {
+  if (!NT) return *p;
+  const f64x2_ld v = __builtin_nontemporal_load(reinterpret_cast<const f64x2_ld*>(p));
+  return make_double2(v.x, v.y);
 }
 
 __device__ __forceinline__ const double2* vec_at(const double2* base, long ld, const int* slot, int j) {
   return base + (long)(slot ? slot[j] : j) * ld;
 }
 
+// The DGKS test of a first Gram-Schmidt pass with coefficients c (nc complex) on a vector of squared
+// norm *wn2 (gate.c null: no test, always true): a second pass is needed when the first removed
+// more than half of it, ||c||^2 > (1 - eta^2) ||w||^2 with eta = 1/sqrt(2) and
+// ||w - V c||^2 = ||w||^2 - ||c||^2 for orthonormal V.  Every block of the second pass forms the
+// same sum in the same order, which spares a launch for a flag.
+__device__ __forceinline__ bool gate_open(const TskGate& g, double* lds /* kBlock / 64 */) {
+  if (!g.c) return true;
+  const double* c = reinterpret_cast<const double*>(g.c);
+  __shared__ double cc;
+  double a = 0.0;
+  for (int j = threadIdx.x; j < 2 * g.nc; j += kBlock) a = fma(c[j], c[j], a);
+  a = block_sum<kBlock>(a, lds);
+  if (threadIdx.x == 0) cc = a;
+  __syncthreads();
+  return cc > 0.5 * *g.wn2;
+}
+
 // part is column-major [2*nv][gridDim.x]: Re/Im of <V_j, w> partial of this block; with_norm
-// adds column 2*nv, the block's partial of ||w||^2 (w is in registers already).  gate: when
-// non-null and *gate == 0, the pass is skipped and the block writes zero partials.
+// adds column 2*nv, the block's partial of ||w||^2 (w is in registers already).  Block (x, y) covers
+// EPT elements per thread of the kDotsNV vectors from y * kDotsNV on, two vectors' loads in flight;
+// w is read again per vector group (from the Infinity Cache or L2), which costs an eighth of V's
+// bytes and gives short vectors enough blocks.  A closed gate skips the pass (zero partials).
+// Measured: see k_tsk_update.
+template <int EPT, bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_tsk_dots(long n, int nv, const double2* __restrict__ base, long ld, const int* __restrict__ slot,
-           const double2* __restrict__ w, double* __restrict__ part, const double* __restrict__ gate,
-           int with_norm) {
-  __shared__ double2 lds[kBlock / 64][kMaxNV + 1];
+           const double2* __restrict__ w, double* __restrict__ part, TskGate gate, int with_norm) {
+  __shared__ double2 lds[kBlock / 64][kDotsNV + 1];
+  __shared__ double glds[kBlock / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int ncol = nv + (with_norm ? 1 : 0);
-  if (gate && *gate == 0.0) {
-    for (int j = threadIdx.x; j < 2 * ncol; j += kBlock) part[(long)j * gridDim.x + blockIdx.x] = 0.0;
+  const int j0 = blockIdx.y * kDotsNV, nj = min(kDotsNV, nv - j0);
+  const bool norm = with_norm && blockIdx.y == 0;
+  if (!gate_open(gate, glds)) {
+    for (int j = threadIdx.x; j < 2 * nj; j += kBlock) part[(long)(2 * j0 + j) * gridDim.x + blockIdx.x] = 0.0;
     return;
   }
-  const long stride = (long)gridDim.x * kBlock;
-  const long i0 = (long)blockIdx.x * kBlock + threadIdx.x;
-  double2 wr[kEPT];
+  constexpr long stride = kBlock;
+  const long i0 = (long)blockIdx.x * (kBlock * EPT) + threadIdx.x;
+  double2 wr[EPT];
 #pragma unroll
-  for (int r = 0; r < kEPT; ++r) {
+  for (int r = 0; r < EPT; ++r) {
     const long i = i0 + r * stride;
     wr[r] = i < n ? w[i] : make_double2(0.0, 0.0);
   }
-  for (int j = 0; j < nv; ++j) {
-    const double2* v = vec_at(base, ld, slot, j);
-    double re = 0.0, im = 0.0;
+  for (int j = 0; j < nj; j += 2) {
+    const bool two = j + 1 < nj;
+    const double2* v0 = vec_at(base, ld, slot, j0 + j);
+    const double2* v1 = vec_at(base, ld, slot, j0 + (two ? j + 1 : j));
+    double2 x0[EPT], x1[EPT];
 #pragma unroll
-    for (int r = 0; r < kEPT; ++r) {
+    for (int r = 0; r < EPT; ++r) {
       const long i = i0 + r * stride;
-      if (i < n) {
-        const double2 x = v[i];
-        re = fma(x.x, wr[r].x, re);
-        re = fma(x.y, wr[r].y, re);
-        im = fma(x.x, wr[r].y, im);
-        im = fma(-x.y, wr[r].x, im);
-      }
+      x0[r] = i < n ? ld_vec<NT>(v0 + i) : make_double2(0.0, 0.0);
+      x1[r] = two && i < n ? ld_vec<NT>(v1 + i) : make_double2(0.0, 0.0);
     }
-    re = wave_sum(re);
-    im = wave_sum(im);
-    if (lane == 0) lds[wid][j] = make_double2(re, im);
+    double re0 = 0.0, im0 = 0.0, re1 = 0.0, im1 = 0.0;
+#pragma unroll
+    for (int r = 0; r < EPT; ++r) {
+      re0 = fma(x0[r].x, wr[r].x, re0);
+      re1 = fma(x1[r].x, wr[r].x, re1);
+      re0 = fma(x0[r].y, wr[r].y, re0);
+      re1 = fma(x1[r].y, wr[r].y, re1);
+      im0 = fma(x0[r].x, wr[r].y, im0);
+      im1 = fma(x1[r].x, wr[r].y, im1);
+      im0 = fma(-x0[r].y, wr[r].x, im0);
+      im1 = fma(-x1[r].y, wr[r].x, im1);
+    }
+    re0 = wave_sum(re0);
+    im0 = wave_sum(im0);
+    re1 = wave_sum(re1);
+    im1 = wave_sum(im1);
+    if (lane == 0) {
+      lds[wid][j] = make_double2(re0, im0);
+      if (two) lds[wid][j + 1] = make_double2(re1, im1);
+    }
   }
-  if (with_norm) {
+  if (norm) {
     double nn = 0.0;
 #pragma unroll
-    for (int r = 0; r < kEPT; ++r) nn = fma(wr[r].x, wr[r].x, fma(wr[r].y, wr[r].y, nn));
+    for (int r = 0; r < EPT; ++r) nn = fma(wr[r].x, wr[r].x, fma(wr[r].y, wr[r].y, nn));
     nn = wave_sum(nn);
-    if (lane == 0) lds[wid][nv] = make_double2(nn, 0.0);
+    if (lane == 0) lds[wid][kDotsNV] = make_double2(nn, 0.0);
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < ncol; j += kBlock) {
+  const int t = threadIdx.x;
+  if (t < nj || (norm && t == kDotsNV)) {
     double re = 0.0, im = 0.0;
 #pragma unroll
     for (int q = 0; q < kBlock / 64; ++q) {
-      re += lds[q][j].x;
-      im += lds[q][j].y;
+      re += lds[q][t].x;
+      im += lds[q][t].y;
     }
+    const int j = t < nj ? j0 + t : nv;
     part[(long)(2 * j) * gridDim.x + blockIdx.x] = re;
-    part[(long)(2 * j + 1) * gridDim.x + blockIdx.x] = im;
+    if (t < nj) part[(long)(2 * j + 1) * gridDim.x + blockIdx.x] = im;
   }
 }
 
-// w += sgn * sum_j c_j V_j ; c complex (interleaved) in device memory.
+// w += sgn * sum_j c_j V_j ; c complex (interleaved) in device memory.  NORM: the block's partial of
+// the new ||w||^2 (also when a closed gate leaves w as it is), which spares a pass over w and a
+// launch.  A block owns one run of elements.  The vectors are walked downwards, since the dots before
+// this pass walked them upwards and the last ones are still in cache (8^3 x 16: 12.1 -> 10.3 us).
+// Bound by the reads of V: over 60 vectors of 16^3 x 32 (1.5 GB) 280 us, 5.6 TB/s, and the dots 265 us
+// (320 before, with one block row for all vectors); over about 31 vectors of 8^3 x 16, from cache, the
+// dots take 14 us (95 before, on 48 CUs).
+template <bool NORM, bool NT>
 __global__ void __launch_bounds__(kBlock)
 k_tsk_update(long n, int nv, const double2* __restrict__ base, long ld, const int* __restrict__ slot,
-             const double2* __restrict__ c, double sgn, double2* __restrict__ w, const double* __restrict__ gate) {
-  if (gate && *gate == 0.0) return;
+             const double2* __restrict__ c, double sgn, double2* __restrict__ w, TskGate gate,
+             double* __restrict__ part) {
   __shared__ double2 cs[kMaxNV];
-  for (int j = threadIdx.x; j < nv; j += kBlock) cs[j] = make_double2(sgn * c[j].x, sgn * c[j].y);
-  __syncthreads();
-  const long stride = (long)gridDim.x * kBlock;
-  for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
+  __shared__ double lds[kBlock / 64];
+  const bool open = gate_open(gate, lds);
+  if (!NORM && !open) return;
+  if (open) {
+    for (int j = threadIdx.x; j < nv; j += kBlock) cs[j] = make_double2(sgn * c[j].x, sgn * c[j].y);
+    __syncthreads();
+  }
+  const long chunk = ((n + gridDim.x - 1) / gridDim.x + kBlock - 1) / kBlock * kBlock;
+  const long i1 = min(n, ((long)blockIdx.x + 1) * chunk);
+  double nn = 0.0;
+  for (long i = (long)blockIdx.x * chunk + threadIdx.x; i < i1; i += kBlock) {
     double2 acc = w[i];
-    for (int j = 0; j < nv; ++j) acc = c_fma(cs[j], vec_at(base, ld, slot, j)[i], acc);
-    w[i] = acc;
+    if (open) {
+#pragma unroll 8
+      for (int j = nv - 1; j >= 0; --j) acc = c_fma(cs[j], ld_vec<NT>(vec_at(base, ld, slot, j) + i), acc);
+      w[i] = acc;
+    }
+    if (NORM) nn = fma(acc.x, acc.x, fma(acc.y, acc.y, nn));
+  }
+  if (NORM) {
+    __syncthreads();  // lds is reused
+    const double s = block_sum<kBlock>(nn, lds);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
   }
 }
 
@@ -312,38 +391,43 @@ static int stream_blocks(long n) {
 }
 
 int tsk_dots(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
-             const double2* w, double* part, const double* gate, int with_norm) {
+             const double2* w, double* part, const TskGate& gate, int with_norm) {
   if (nv > kMaxNV) fail(DL_E_INVALID, "too many basis vectors (max 512)");
   const int nb = tsk_nblocks(n);
   if (nv > 0 || with_norm) {
-    hipLaunchKernelGGL(k_tsk_dots, dim3(nb), dim3(kBlock), 0, s, n, nv, base, ld, slot, w, part, gate, with_norm);
+    const dim3 grid(nb, std::max(1, (nv + kDotsNV - 1) / kDotsNV));
+#define DL_DOTS(E, N) \
+  hipLaunchKernelGGL((k_tsk_dots<E, N>), grid, dim3(kBlock), 0, s, n, nv, base, ld, slot, w, part, gate, with_norm)
+    if (dots_ept(n) == 8) {
+      if (streams(n, nv)) DL_DOTS(8, true);
+      else DL_DOTS(8, false);
+    } else {
+      if (streams(n, nv)) DL_DOTS(2, true);
+      else DL_DOTS(2, false);
+    }
+#undef DL_DOTS
     DL_HIP(hipGetLastError());
   }
   return nb;
 }
 
-void tsk_update(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
-                const double2* c, double sgn, double2* w, const double* gate) {
+int tsk_update(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
+               const double2* c, double sgn, double2* w, const TskGate& gate, double* norm_part) {
   if (nv > kMaxNV) fail(DL_E_INVALID, "too many basis vectors (max 512)");
-  if (nv <= 0) return;
-  hipLaunchKernelGGL(k_tsk_update, dim3(stream_blocks(n)), dim3(kBlock), 0, s, n, nv, base, ld, slot, c, sgn, w,
-                     gate);
+  const int nb = stream_blocks(n);
+  if (nv <= 0 && !norm_part) return nb;
+#define DL_UPD(O, N) \
+  hipLaunchKernelGGL((k_tsk_update<O, N>), dim3(nb), dim3(kBlock), 0, s, n, nv, base, ld, slot, c, sgn, w, gate, norm_part)
+  if (norm_part) {
+    if (streams(n, nv)) DL_UPD(true, true);
+    else DL_UPD(true, false);
+  } else {
+    if (streams(n, nv)) DL_UPD(false, true);
+    else DL_UPD(false, false);
+  }
+#undef DL_UPD
   DL_HIP(hipGetLastError());
-}
-
-// gate = 1 if the first Gram-Schmidt pass removed more than the DGKS share of w, that is
-// ||c||^2 > (1 - eta^2) ||w||^2 with ||w - V c||^2 = ||w||^2 - ||c||^2 for orthonormal V, else 0.
-__global__ void k_dgks_gate(const double* __restrict__ c, int nv, const double* __restrict__ wn2, double eta2,
-                            double* __restrict__ gate) {
-  double cc = 0.0;
-  for (int j = threadIdx.x; j < 2 * nv; j += blockDim.x) cc = fma(c[j], c[j], cc);
-  cc = wave_sum(cc);  // one wave
-  if (threadIdx.x == 0) *gate = cc > (1.0 - eta2) * *wn2 ? 1.0 : 0.0;
-}
-
-void tsk_dgks_gate(hipStream_t s, const double* c, int nv, const double* wn2, double eta2, double* gate) {
-  hipLaunchKernelGGL(k_dgks_gate, dim3(1), dim3(64), 0, s, c, nv, wn2, eta2, gate);
-  DL_HIP(hipGetLastError());
+  return nb;
 }
 
 // Zero-filled device doubles (at least ndouble) for timing read-modify-write launches with no

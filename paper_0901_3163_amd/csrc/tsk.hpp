@@ -27,19 +27,28 @@ TskCfg tsk_choose(hipStream_t s, int kind, long n, int nv, int nw, const std::ve
 // Tune one key on buffers of its own (dl_tune_tsk).
 TskCfg tsk_tune(hipStream_t s, int kind, long n, int nv, int nw, int reps, double* best_us);
 
-// Partial count tsk_dots uses for length n (partials are [2*nv][nblocks]).
+// The gate of a second Gram-Schmidt pass: open when the first pass, with coefficients c (nc
+// complex) on a vector of squared norm *wn2 (device memory), removed more than half of it; c null:
+// always open.
+struct TskGate {
+  const double2* c = nullptr;
+  int nc = 0;
+  const double* wn2 = nullptr;
+};
+
+// Partial count tsk_dots uses for length n (partials are [2*nv][nblocks]): ceil(n / 2048), or
+// ceil(n / 512) while that is below 256 * 4.
 int tsk_nblocks(long n);
 // part <- partials of c = V^H w (sum with sum_partials(part, nb, 2*nv, c)). Returns nb.
-// with_norm: partial column 2*nv holds ||w||^2 (part needs 2*(nv+1)*nb doubles).  gate (device,
-// may be NULL): *gate == 0 skips the pass, leaving zero partials.
+// with_norm: partial column 2*nv holds ||w||^2 (part needs 2*(nv+1)*nb doubles).  A closed gate
+// skips the pass, leaving zero partials.
 int tsk_dots(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
-             const double2* w, double* part, const double* gate = nullptr, int with_norm = 0);
-// w <- w + sgn * V c, c: nv complex in device memory; *gate == 0 (gate non-null) skips it.
-void tsk_update(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
-                const double2* c, double sgn, double2* w, const double* gate = nullptr);
-// The DGKS test after a first Gram-Schmidt pass with coefficients c (nv complex) of a vector w
-// of squared norm *wn2: *gate = 1 (a second pass is needed) when ||c||^2 > (1 - eta2) *wn2.
-void tsk_dgks_gate(hipStream_t s, const double* c, int nv, const double* wn2, double eta2, double* gate);
+             const double2* w, double* part, const TskGate& gate = TskGate(), int with_norm = 0);
+// w <- w + sgn * V c, c: nv complex in device memory; a closed gate skips it.  norm_part (may be
+// NULL): partials of the resulting ||w||^2, one per block; returns the block count.
+int tsk_update(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
+               const double2* c, double sgn, double2* w, const TskGate& gate = TskGate(),
+               double* norm_part = nullptr);
 // Y_l (+)= sum_j G[j*ldg + l] V_j for l < ny; output l at obase + (oslot ? oslot[l] : l) * old.
 void tsk_combine(hipStream_t s, long n, int nv, const double2* base, long ld, const int* slot,
                  const double* G, int ldg, int ny, double2* obase, long old, const int* oslot,

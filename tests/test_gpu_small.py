@@ -37,3 +37,21 @@ def test_first_solve_over_basis_sizes(gpu_ctx, c1_config, kind, m, k):
         assert abs(np.linalg.norm(a - ev[i] * Y[i]) - res[i]) < 1e-11
     eig.close()
     op.close()
+
+
+@pytest.mark.parametrize("n,nv", [(511, 8), (513, 9), (522240, 17), (522241, 16), (2049, 1), (1048576, 17)])
+def test_projection_edges(gpu_ctx, n, nv):
+    """c = V^H w and w - V c at the edges of the dots' blocks: elements per thread (2 below 256
+    blocks of 2048), groups of 8 vectors, odd counts, a basis just above the Infinity Cache.
+    Sums of n products of unit Gaussians: rounding below 1e-13 of ||V_j|| ||w|| (FP64)."""
+    import torch
+    from paper_0901_3163_amd import deflan
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + nv)
+    V = torch.view_as_complex(torch.randn((nv, n, 2), generator=g, device="cuda", dtype=torch.float64))
+    w = torch.view_as_complex(torch.randn((n, 2), generator=g, device="cuda", dtype=torch.float64))
+    c, w2 = deflan.dl_tsk_project(gpu_ctx, V, w, subtract=True)
+    ref = (V.conj() * w).sum(1)
+    assert float((c - ref).abs().max()) < 1e-13 * 2 * n
+    out = w - (ref[:, None] * V).sum(0)
+    assert float((w2 - out).abs().max()) < 1e-12 * float(ref.abs().max()) * nv
