@@ -48,9 +48,9 @@ void need(bool ok, const char* msg) {
 void use_device(dl_ctx* ctx) { DL_HIP(hipSetDevice(ctx->device)); }
 
 // nfield fields in the caller's layout on lattice `lat` -> tiled device fields at t (pads zeroed).
-void fields_in_lat(dl_op* op, const Lattice& lat, const double* p, int nfield, int mem, double2* t) {
+template <class SV>
+void fields_in_lat(dl_op* op, const Lattice& lat, const double* p, int nfield, int mem, SV* t) {
   hipStream_t s = op->ctx->stream;
-  zero(s, (long)nfield * lat.nc, t);
   const size_t bytes = (size_t)nfield * lat.V * kSpin * sizeof(double2);
   if (mem == DL_DEVICE) {
     pack_spinor(s, lat, reinterpret_cast<const double2*>(p), t, nfield);
@@ -62,7 +62,8 @@ void fields_in_lat(dl_op* op, const Lattice& lat, const double* p, int nfield, i
   }
 }
 
-void fields_in_to(dl_op* op, const double* p, int nfield, int mem, double2* t) {
+template <class SV>
+void fields_in_to(dl_op* op, const double* p, int nfield, int mem, SV* t) {
   fields_in_lat(op, op->lat, p, nfield, mem, t);
 }
 
@@ -72,7 +73,8 @@ DBuf<double2> fields_in(dl_op* op, const double* p, int nfield, int mem) {
   return t;
 }
 
-void fields_out_lat(dl_op* op, const Lattice& lat, const double2* t, double* p, int nfield, int mem) {
+template <class SV>
+void fields_out_lat(dl_op* op, const Lattice& lat, const SV* t, double* p, int nfield, int mem) {
   hipStream_t s = op->ctx->stream;
   const size_t bytes = (size_t)nfield * lat.V * kSpin * sizeof(double2);
   if (mem == DL_DEVICE) {
@@ -85,7 +87,8 @@ void fields_out_lat(dl_op* op, const Lattice& lat, const double2* t, double* p, 
   DL_HIP(hipStreamSynchronize(s));
 }
 
-void fields_out(dl_op* op, const double2* t, double* p, int nfield, int mem) {
+template <class SV>
+void fields_out(dl_op* op, const SV* t, double* p, int nfield, int mem) {
   fields_out_lat(op, op->lat, t, p, nfield, mem);
 }
 
@@ -394,17 +397,20 @@ int dl_apply(dl_op* op, int which, const double* in, double* out, int mem) {
     need(mem == DL_HOST || mem == DL_DEVICE, "mem must be DL_HOST or DL_DEVICE");
     need(in != out, "in and out may not alias");
     use_device(op->ctx);
-    DBuf<double2> t = fields_in(op, in, 1, mem);
-    DBuf<double2> r(op->lat.nc), tmp(op->lat.nc);
-    zero(op->ctx->stream, op->lat.nc, r.get());
-    zero(op->ctx->stream, op->lat.nc, tmp.get());
+    // one buffer for the input (and the result of M^dag M) and the result (the middle of M^dag M);
+    // the stencil writes every element, padding sites included
+    const long nc = op->lat.nc;
+    DBuf<double2> f(2 * (size_t)nc);
+    double2 *t = f.get(), *r = f.get() + nc;
+    fields_in_to(op, in, 1, mem, t);
     if (which == DL_APPLY_MDAGM) {
-      apply_wilson(op, 0, t.get(), tmp.get());
-      apply_wilson(op, 1, tmp.get(), r.get());
+      apply_wilson(op, 0, t, r);
+      apply_wilson(op, 1, r, t);
+      std::swap(t, r);
     } else {
-      apply_wilson(op, which, t.get(), r.get());
+      apply_wilson(op, which, t, r);
     }
-    fields_out(op, r.get(), out, 1, mem);
+    fields_out(op, r, out, 1, mem);
     return DL_OK;
   });
 }
@@ -463,8 +469,7 @@ int dl_solve_next(dl_op* op, const dl_eig* eig, int nrhs, const double* B, doubl
       fail(DL_E_MISMATCH, "eigenvector handle was built for a different operator");
     DBuf<double2> bt = fields_in(op, B, nrhs, mem);
     DBuf<double2> xt = o.x0_given ? fields_in(op, X, nrhs, mem) : DBuf<double2>((size_t)nrhs * op->lat.nc);
-    if (!o.x0_given) zero(op->ctx->stream, (long)nrhs * op->lat.nc, xt.get());
-    HistoryReq hr(stats, nrhs);
+    HistoryReq hr(stats, nrhs);  // (without x0 the solvers start x at zero themselves)
     const int rc = o.batched ? solve_next_batched(op, eig, nrhs, bt.get(), xt.get(), tol, o, stats, hr.get())
                              : solve_next(op, eig, nrhs, bt.get(), xt.get(), tol, o, stats, hr.get());
     fields_out(op, xt.get(), X, nrhs, mem);
@@ -487,28 +492,20 @@ int dl_apply_batched(dl_op* op, int which, int prec, int nrhs, const double* in,
     hipStream_t s = op->ctx->stream;
     const Lattice& lat = op->lat;
     const long n = (long)nrhs * lat.nc;
-    DBuf<double2> t = fields_in(op, in, nrhs, mem);
-    DBuf<double2> r(n);
     const WilsonCfg cfg = wilson_cfg(op, prec, nrhs);
-    if (prec == DL_FP64) {
-      wilson_batched<double>(s, lat, op->U.get(), op->kappa, which, t.get(), r.get(), lat.nc, nrhs, 0, nullptr,
-                             nullptr, nullptr, cfg);
-    } else if (prec == DL_FP32) {
-      DBuf<float2> a32(n), b32(n);
-      round_f32(s, n, t.get(), a32.get());
-      wilson_batched<float>(s, lat, op_links32_public(op), op->kappa, which, a32.get(), b32.get(), lat.nc, nrhs, 0,
-                            nullptr, nullptr, nullptr, cfg);
-      widen_f64(s, n, b32.get(), r.get());
-      DL_HIP(hipStreamSynchronize(s));
-    } else {
-      DBuf<bf2> a16(n), b16(n);
-      round_bf16(s, n, t.get(), a16.get());
-      wilson_batched<float>(s, lat, op_links32_public(op), op->kappa, which, a16.get(), b16.get(), lat.nc, nrhs, 0,
-                            nullptr, nullptr, nullptr, cfg);
-      widen_bf16(s, n, b16.get(), r.get());
-      DL_HIP(hipStreamSynchronize(s));
-    }
-    fields_out(op, r.get(), out, nrhs, mem);
+    // the fields are rounded to the storage as they are tiled, and widened as they go back
+    auto go = [&](auto R0, auto SV0, const auto* U) {
+      using R = decltype(R0);
+      using SV = decltype(SV0);
+      DBuf<SV> f(2 * (size_t)n);
+      fields_in_to(op, in, nrhs, mem, f.get());
+      wilson_batched<R>(s, lat, U, op->kappa, which, f.get(), f.get() + n, lat.nc, nrhs, 0, nullptr, nullptr, nullptr,
+                        cfg);
+      fields_out(op, f.get() + n, out, nrhs, mem);
+    };
+    if (prec == DL_FP64) go(double{}, double2{}, op->U.get());
+    else if (prec == DL_FP32) go(float{}, float2{}, op_links32_public(op));
+    else go(float{}, bf2{}, op_links32_public(op));
     return DL_OK;
   });
 }

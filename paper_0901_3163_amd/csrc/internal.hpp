@@ -142,8 +142,11 @@ struct TimeScope {
 };
 
 // ---- launchers: layout ------------------------------------------------------
-void pack_spinor(hipStream_t s, const Lattice& lat, const double2* host_layout, double2* tiled, int nfield);
-void unpack_spinor(hipStream_t s, const Lattice& lat, const double2* tiled, double2* host_layout, int nfield);
+// SV: storage of the tiled side (double2, float2 or bf2).  Padding sites are written as zeros.
+template <class SV>
+void pack_spinor(hipStream_t s, const Lattice& lat, const double2* host_layout, SV* tiled, int nfield);
+template <class SV>
+void unpack_spinor(hipStream_t s, const Lattice& lat, const SV* tiled, double2* host_layout, int nfield);
 void pack_links(hipStream_t s, const Lattice& lat, const double2* host_layout, double2* tiled);
 
 // ---- launchers: Wilson operator ------------------------------------------------

@@ -10,6 +10,7 @@ raises.
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 import weakref
 
@@ -194,12 +195,14 @@ def _c128(a):
     return a
 
 
-def _empty_like(a, shape=None):
-    shape = a.shape if shape is None else shape
+def _empty_like(a, shape=None, writes=None):
+    """An output array for a call that writes `writes` elements (None: all); zeroed if that leaves some."""
+    shape = tuple(a.shape if shape is None else shape)
+    whole = writes is None or writes == math.prod(shape)
     if isinstance(a, np.ndarray):
-        return np.zeros(shape, dtype=np.complex128)
+        return (np.empty if whole else np.zeros)(shape, dtype=np.complex128)
     import torch
-    return torch.zeros(shape, dtype=torch.complex128, device=a.device)
+    return (torch.empty if whole else torch.zeros)(shape, dtype=torch.complex128, device=a.device)
 
 
 # ---------------------------------------------------------------------------
@@ -328,7 +331,7 @@ class Operator:
 
     def apply(self, which: int, psi):
         psi = _c128(psi)
-        out = _empty_like(psi)
+        out = _empty_like(psi, writes=12 * self.V)
         pi, mem = _ptr(psi)
         po, _ = _ptr(out)
         _check(lib.dl_apply(self.h, int(which), pi, po, mem))
@@ -337,7 +340,7 @@ class Operator:
     def apply_batched(self, which: int, prec: int, Psi):
         """op(psi_j) for each field of Psi ([n][V][4][3]) by the multi-rhs stencil (FP64 or FP32)."""
         Psi = _c128(Psi)
-        out = _empty_like(Psi)
+        out = _empty_like(Psi, writes=12 * self.V * int(Psi.shape[0]))
         pi, mem = _ptr(Psi)
         po, _ = _ptr(out)
         _check(lib.dl_apply_batched(self.h, int(which), int(prec), int(Psi.shape[0]), pi, po, mem))
@@ -346,7 +349,7 @@ class Operator:
     def eo_prepare(self, b):
         """bhat = b_e + kappa D_eo b_o (even half field) for a whole-lattice b (DL_EVEN_ODD operators)."""
         b = _c128(b)
-        bh = _empty_like(b, (self.V,) + tuple(b.shape[1:]))
+        bh = _empty_like(b, (self.V,) + tuple(b.shape[1:]), writes=12 * self.V)
         pb, mem = _ptr(b)
         ph, _ = _ptr(bh)
         _check(lib.dl_eo_prepare(self.h, pb, ph, mem))
@@ -355,7 +358,7 @@ class Operator:
     def eo_reconstruct(self, b, xe):
         """The whole-lattice solution from the even-site one (DL_EVEN_ODD operators)."""
         b, xe = _c128(b), _c128(xe)
-        x = _empty_like(b)
+        x = _empty_like(b, writes=12 * self.V_full)
         pb, mem = _ptr(b)
         pxe, _ = _ptr(xe)
         px, _ = _ptr(x)
@@ -377,7 +380,7 @@ class Operator:
                     want_eig=True, reorth=DL_REORTH_FULL, reorth_period=0, history=0):
         """history > 0: the stats dict also holds 'history', an array of (mvp, relres) rows."""
         b = _c128(b)
-        x = _empty_like(b)
+        x = _empty_like(b, writes=12 * self.V)
         o = dl_first_opts(eig_tol or 0.0, past_conv_factor or 0.0, int(max_mvp or 0), int(reorth),
                           int(reorth_period))
         st, bufs = _stats(1, history)
@@ -394,7 +397,7 @@ class Operator:
                    net_prec=DL_FP32, method=0, minres_window=0, history=0):
         B = _c128(B)
         nrhs = B.shape[0]
-        X = _empty_like(B) if x0 is None else _c128(x0).copy()
+        X = _empty_like(B, writes=12 * self.V * nrhs) if x0 is None else _c128(x0).copy()
         o = dl_next_opts(int(storage), int(reliable_every or 0), int(batched), 1 if x0 is not None else 0,
                          int(max_mvp or 0), net.h if net is not None else None, 1 if graph else 0,
                          float(inner_drop or 0.0), int(eig_storage), int(net_prec), int(method),
@@ -468,7 +471,7 @@ class Net:
     def apply(self, op: "Operator", B, prec=None):
         """net(b) for each field of B ([n][V][4][3]); prec DL_BF16: BF16 matrix-core inference."""
         B = _c128(B)
-        Y = _empty_like(B)
+        Y = _empty_like(B, writes=12 * op.V * int(B.shape[0]))
         pB, mem = _ptr(B)
         pY, _ = _ptr(Y)
         if prec is None:
@@ -527,7 +530,7 @@ def solve_next_multi(ctx: Context, items, reliable_every=None, max_mvp=None, x0s
     keep, Xs, mem = [], [], None
     for i, (op, eig, B, tol) in enumerate(items):
         B = _c128(B)
-        X = _empty_like(B) if x0s is None else _c128(x0s[i]).copy()
+        X = (_empty_like(B, writes=12 * op.V * int(B.shape[0])) if x0s is None else _c128(x0s[i]).copy())
         pB, m = _ptr(B)
         pX, _ = _ptr(X)
         if mem is None:

@@ -55,3 +55,22 @@ def test_projection_edges(gpu_ctx, n, nv):
     assert float((c - ref).abs().max()) < 1e-13 * 2 * n
     out = w - (ref[:, None] * V).sum(0)
     assert float((w2 - out).abs().max()) < 1e-12 * float(ref.abs().max()) * nv
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (3, 5, 2, 4), (5, 3, 3, 3), (4, 2, 2, 9)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "bf16"])
+def test_layout_conversions_round_trip(gpu_ctx, dims, prec):
+    """With kappa = 0 the batch apply is the storage's rounding of its input, whole and in order,
+    on lattices whose last tile is ragged, and in both kinds of memory; FP64 is bitwise."""
+    import torch
+    from paper_0901_3163_amd import deflan
+    from lattice_inputs import su3_links
+    op = deflan.Operator(gpu_ctx, dims, su3_links(dims, 3), 0.0, deflan.DL_G5M)
+    x = np.stack([gaussian_spinor(dims, 50 + i) for i in range(3)])
+    y = op.apply_batched(0, {"f64": 0, "f32": 1, "bf16": 2}[prec], x)
+    t = torch.view_as_real(torch.from_numpy(x))
+    ref = {"f64": t, "f32": t.float().double(), "bf16": t.float().bfloat16().double()}[prec]
+    assert np.array_equal(y, torch.view_as_complex(ref).numpy())
+    z = op.apply_batched(0, {"f64": 0, "f32": 1, "bf16": 2}[prec], torch.from_numpy(x).cuda())
+    assert np.array_equal(z.cpu().numpy(), y)
+    op.close()
