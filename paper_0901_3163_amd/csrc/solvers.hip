@@ -49,9 +49,10 @@ enum {
   S_NRM,          // norm
   // CGLS
   S_SS, S_QQ, S_ALPHA, S_BETA,
-  // MinRes
-  M_ALPHA, M_BETA, M_BNEXT, M_COLD, M_SOLD, M_C, M_S, M_ETA, M_TAU, M_DELTA, M_EPS, M_GAMMA,
-  S_COUNT
+  S_SS2,          // the other of the two alternating slots of S_SS
+  // MinRes: residual estimate, and two alternating state blocks
+  M_ETA, M_STATE, M_STATE2 = M_STATE + 8,
+  S_COUNT = M_STATE2 + 8
 };
 
 // ---- finalisation kernels (one block) --------------------------------------
@@ -79,32 +80,6 @@ __global__ void __launch_bounds__(kBlock) k_fin_norm(const double* part, int np,
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_fin_cgls_alpha(const double* part, int np, double* sc) {
-  __shared__ double lds[kBlock / 64];
-  const double qq = fin_sum(part, np, lds);
-  if (threadIdx.x == 0) {
-    sc[S_QQ] = qq;
-    const bool ok = qq > 0.0 && isfinite(qq) && sc[S_FLAG] == 0.0;
-    sc[S_ALPHA] = ok ? sc[S_SS] / qq : 0.0;
-    if (!ok) sc[S_FLAG] = 1.0;
-  }
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_fin_cgls_beta(const double* ps, int nps, const double* pr, int npr, double* sc) {
-  __shared__ double lds[kBlock / 64];
-  const double ss = fin_sum(ps, nps, lds);
-  const double rr = fin_sum(pr, npr, lds);
-  if (threadIdx.x == 0) {
-    const double old = sc[S_SS];
-    const bool ok = old > 0.0 && isfinite(ss) && sc[S_FLAG] == 0.0;
-    sc[S_BETA] = ok ? ss / old : 0.0;
-    if (ok) sc[S_SS] = ss;
-    else sc[S_FLAG] = 1.0;
-    sc[S_RN2] = rr;
-  }
-}
-
 // CG on a Hermitian A (positive or not): alpha = ||r||^2 / Re(p^H A p); breakdown if p^H A p = 0.
 __global__ void __launch_bounds__(kBlock) k_fin_cg_alpha(const double* part, int np, double* sc) {
   __shared__ double lds[kBlock / 64];
@@ -127,46 +102,6 @@ __global__ void __launch_bounds__(kBlock) k_fin_cg_beta(const double* part, int 
     sc[S_BETA] = ok ? rr / old : 0.0;
     sc[S_RN2] = rr;
     if (!ok) sc[S_FLAG] = 1.0;
-  }
-}
-
-// MinRes: Givens QR of the new tridiagonal column (beta_j, alpha_j, beta_{j+1}).
-__global__ void __launch_bounds__(kBlock) k_fin_minres_rot(const double* part, int np, double* sc) {
-  __shared__ double lds[kBlock / 64];
-  const double ww = fin_sum(part, np, lds);
-  if (threadIdx.x == 0) {
-    const double bnext = sqrt(ww);
-    const double beta = sc[M_BETA], alpha = sc[M_ALPHA];
-    const double c_old = sc[M_COLD], s_old = sc[M_SOLD], c = sc[M_C], s = sc[M_S];
-    const double eps = s_old * beta;
-    const double dt = c_old * beta;
-    const double delta = c * dt + s * alpha;
-    const double gbar = -s * dt + c * alpha;
-    const double gamma = hypot(gbar, bnext);
-    const bool ok = gamma > 0.0 && isfinite(gamma) && isfinite(bnext) && sc[S_FLAG] == 0.0;
-    if (ok) {
-      const double cn = gbar / gamma, sn = bnext / gamma;
-      const double eta = sc[M_ETA];
-      sc[M_TAU] = cn * eta;
-      sc[M_ETA] = -sn * eta;
-      sc[M_EPS] = eps;
-      sc[M_DELTA] = delta;
-      sc[M_GAMMA] = gamma;
-      sc[M_COLD] = c;
-      sc[M_SOLD] = s;
-      sc[M_C] = cn;
-      sc[M_S] = sn;
-      sc[M_BNEXT] = bnext;
-      sc[M_BETA] = bnext;
-      if (!(bnext > 0.0)) sc[S_FLAG] = 2.0;  // invariant subspace: the solution is exact
-    } else {
-      sc[M_TAU] = 0.0;
-      sc[M_EPS] = 0.0;
-      sc[M_DELTA] = 0.0;
-      sc[M_GAMMA] = 1.0;
-      if (sc[S_FLAG] == 0.0) sc[S_FLAG] = 1.0;
-    }
-    sc[S_RN2] = sc[M_ETA] * sc[M_ETA];
   }
 }
 
@@ -255,11 +190,81 @@ k_xpay(long n, const double* sc, int idx, const double2* __restrict__ s, double2
     p[i] = c_axpy(b, p[i], s[i]);
 }
 
-// w = w - alpha v - beta vprev ; partial ||w||^2
+// ---- scalar recurrences inside the streaming kernels ----------------------------------
+// A one-rhs iteration on a small lattice is a chain of short launches (3-4 us each), so the scalars
+// have no launches of their own: every block of a streaming kernel sums the partials before it in
+// the same fixed order and forms the same scalar, and block 0 stores it.  What a later iteration
+// overwrites while other blocks still read it is held twice and alternates (old -> new index).
+// CGLS at 8^4: 6 launches an iteration -> 4.
+
+// alpha = ss / ||q||^2, ss = sc[i_ss]; x += alpha p ; r -= alpha q ; partial ||r||^2
 __global__ void __launch_bounds__(kBlock)
-k_lanczos3(long n, const double* sc, const double2* __restrict__ v, const double2* __restrict__ vp,
-           double2* __restrict__ w, double* __restrict__ part) {
-  const double a = sc[M_ALPHA], b = sc[M_BETA];
+k_cgls_step1(long n, const double* __restrict__ pq, int npq, double* sc, int i_ss, const double2* __restrict__ p,
+             const double2* __restrict__ q, double2* __restrict__ x, double2* __restrict__ r,
+             double* __restrict__ part) {
+  __shared__ double lds[kBlock / 64];
+  __shared__ double sh_a;
+  const double qq = fin_sum(pq, npq, lds);
+  if (threadIdx.x == 0) {
+    const bool ok = qq > 0.0 && isfinite(qq) && sc[S_FLAG] == 0.0;
+    sh_a = ok ? sc[i_ss] / qq : 0.0;
+    if (blockIdx.x == 0 && !ok) sc[S_FLAG] = 1.0;
+  }
+  __syncthreads();
+  const double a = sh_a;
+  double acc = 0.0;
+  for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
+    x[i] = c_axpy(a, p[i], x[i]);
+    const double2 v = c_axpy(-a, q[i], r[i]);
+    r[i] = v;
+    acc = fma(v.x, v.x, fma(v.y, v.y, acc));
+  }
+  const double s = block_sum<kBlock>(acc, lds);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// beta = ss / sc[i_old], sc[i_new] = ss, sc[S_RN2] = ||r||^2; p = s + beta p
+__global__ void __launch_bounds__(kBlock)
+k_cgls_step2(long n, const double* __restrict__ ps, int nps, const double* __restrict__ pr, int npr, double* sc,
+             int i_old, int i_new, const double2* __restrict__ s, double2* __restrict__ p) {
+  __shared__ double lds[kBlock / 64];
+  __shared__ double sh_b;
+  const double ss = fin_sum(ps, nps, lds);
+  const double rr = blockIdx.x == 0 ? fin_sum(pr, npr, lds) : 0.0;
+  if (threadIdx.x == 0) {
+    const double old = sc[i_old];
+    const bool ok = old > 0.0 && isfinite(ss) && sc[S_FLAG] == 0.0;
+    sh_b = ok ? ss / old : 0.0;
+    if (blockIdx.x == 0) {
+      sc[i_new] = ok ? ss : old;
+      if (!ok) sc[S_FLAG] = 1.0;
+      sc[S_RN2] = rr;
+    }
+  }
+  __syncthreads();
+  const double b = sh_b;
+  for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock)
+    p[i] = c_axpy(b, p[i], s[i]);
+}
+
+// MinRes state of one iteration (offsets in a state block).
+// N_FLAG stops the recurrence; blocks read the old state's, so that one block's verdict cannot reach
+// another within a launch (sc[S_FLAG] tells the host).
+enum { N_ALPHA = 0, N_BETA, N_COLD, N_SOLD, N_C, N_S, N_ETA, N_FLAG };
+
+// w = w - alpha v - beta vprev, alpha from the stencil's partials (stored in st), beta of st; partial ||w||^2
+__global__ void __launch_bounds__(kBlock)
+k_minres_step1(long n, const double* __restrict__ pa, int npa, double* st, const double2* __restrict__ v,
+               const double2* __restrict__ vp, double2* __restrict__ w, double* __restrict__ part) {
+  __shared__ double lds[kBlock / 64];
+  __shared__ double sh_a;
+  const double al = fin_sum(pa, npa, lds);
+  if (threadIdx.x == 0) {
+    sh_a = al;
+    if (blockIdx.x == 0) st[N_ALPHA] = al;
+  }
+  __syncthreads();
+  const double a = sh_a, b = st[N_BETA];
   double acc = 0.0;
   for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
     double2 t = c_axpy(-a, v[i], w[i]);
@@ -267,19 +272,53 @@ k_lanczos3(long n, const double* sc, const double2* __restrict__ v, const double
     w[i] = t;
     acc = fma(t.x, t.x, fma(t.y, t.y, acc));
   }
-  __shared__ double lds[kBlock / 64];
   const double s = block_sum<kBlock>(acc, lds);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
+// Givens QR of the new tridiagonal column (beta_j, alpha_j, beta_{j+1}) from the state st into st_new, then
 // d_new = (v - delta d1 - eps d2)/gamma -> dn ; x += tau d_new ; vn = w / bnext
 __global__ void __launch_bounds__(kBlock)
-k_minres_update(long n, const double* sc, const double2* __restrict__ v, const double2* __restrict__ d1,
-                const double2* d2, double2* dn, double2* __restrict__ x, const double2* __restrict__ w,
-                double2* __restrict__ vn) {
-  const double delta = sc[M_DELTA], eps = sc[M_EPS], ig = 1.0 / sc[M_GAMMA], tau = sc[M_TAU];
-  const double bn = sc[M_BNEXT];
-  const double ib = bn > 0.0 ? 1.0 / bn : 0.0;
+k_minres_step2(long n, const double* __restrict__ pw, int npw, double* sc, const double* __restrict__ st,
+               double* __restrict__ st_new, const double2* __restrict__ v, const double2* __restrict__ d1,
+               const double2* d2, double2* dn, double2* __restrict__ x, const double2* __restrict__ w, double2* vn) {
+  __shared__ double lds[kBlock / 64];
+  __shared__ double sh[5];
+  const double ww = fin_sum(pw, npw, lds);
+  if (threadIdx.x == 0) {
+    const double bnext = sqrt(ww);
+    const double beta = st[N_BETA], alpha = st[N_ALPHA], eta = st[N_ETA];
+    const double c_old = st[N_COLD], s_old = st[N_SOLD], c = st[N_C], s = st[N_S];
+    const double eps = s_old * beta;
+    const double dt = c_old * beta;
+    const double delta = c * dt + s * alpha;
+    const double gbar = -s * dt + c * alpha;
+    const double gamma = hypot(gbar, bnext);
+    const bool ok = gamma > 0.0 && isfinite(gamma) && isfinite(bnext) && st[N_FLAG] == 0.0;
+    const double cn = ok ? gbar / gamma : c, sn = ok ? bnext / gamma : s;
+    sh[0] = ok ? delta : 0.0;
+    sh[1] = ok ? eps : 0.0;
+    sh[2] = ok ? gamma : 1.0;
+    sh[3] = ok ? cn * eta : 0.0;  // tau
+    sh[4] = ok && bnext > 0.0 ? 1.0 / bnext : 0.0;
+    if (blockIdx.x == 0) {
+      const double en = ok ? -sn * eta : eta;
+      st_new[N_ETA] = en;
+      st_new[N_BETA] = ok ? bnext : beta;
+      st_new[N_COLD] = ok ? c : c_old;
+      st_new[N_SOLD] = ok ? s : s_old;
+      st_new[N_C] = cn;
+      st_new[N_S] = sn;
+      sc[M_ETA] = en;
+      sc[S_RN2] = en * en;
+      // 2: invariant subspace, the solution is exact
+      const double flag = st[N_FLAG] != 0.0 ? st[N_FLAG] : !ok ? 1.0 : !(bnext > 0.0) ? 2.0 : 0.0;
+      st_new[N_FLAG] = flag;
+      sc[S_FLAG] = flag;
+    }
+  }
+  __syncthreads();
+  const double delta = sh[0], eps = sh[1], ig = 1.0 / sh[2], tau = sh[3], ib = sh[4];
   for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
     double2 d = c_axpy(-delta, d1[i], v[i]);
     d = c_axpy(-eps, d2[i], d);
@@ -409,18 +448,23 @@ static InnerResult minres_run(dl_op* op, const double2* b, double2* x, double bn
     res.converged = true;
     return res;
   }
-  h[S_FLAG] = 0.0; h[M_BETA] = 0.0; h[M_COLD] = 1.0; h[M_SOLD] = 0.0; h[M_C] = 1.0; h[M_S] = 0.0;
+  h[S_FLAG] = 0.0;
   h[M_ETA] = beta1;
+  double* hs = h + M_STATE;
+  hs[N_ALPHA] = 0.0; hs[N_BETA] = 0.0; hs[N_COLD] = 1.0; hs[N_SOLD] = 0.0; hs[N_C] = 1.0; hs[N_S] = 0.0;
+  hs[N_ETA] = beta1; hs[N_FLAG] = 0.0;
   write_scalars(op->ctx, S.sc.get(), S_COUNT, h);
+  double *st = S.sc.get() + M_STATE, *st_new = S.sc.get() + M_STATE2;
+  double* pw = S.part.get() + kMaxPartials;
   while (res.mvp < max_mvp) {
     const int nbw = apply_wilson(op, 2, v, w, 2, S.part.get());
     res.mvp += 1;
-    hipLaunchKernelGGL(k_fin_store, dim3(1), dim3(kBlock), 0, s, S.part.get(), nbw, S.sc.get(), (int)M_ALPHA);
-    hipLaunchKernelGGL(k_lanczos3, dim3(nb), dim3(kBlock), 0, s, n, S.sc.get(), v, vp, w, S.part.get());
-    hipLaunchKernelGGL(k_fin_minres_rot, dim3(1), dim3(kBlock), 0, s, S.part.get(), nb, S.sc.get());
+    hipLaunchKernelGGL(k_minres_step1, dim3(nb), dim3(kBlock), 0, s, n, S.part.get(), nbw, st, v, vp, w, pw);
     // d_new into d2's buffer; v_next into vp's buffer
-    hipLaunchKernelGGL(k_minres_update, dim3(G), dim3(kBlock), 0, s, n, S.sc.get(), v, d1, d2, d2, x, w, vp);
+    hipLaunchKernelGGL(k_minres_step2, dim3(G), dim3(kBlock), 0, s, n, pw, nb, S.sc.get(), st, st_new, v, d1, d2, d2, x,
+                       w, vp);
     DL_HIP(hipGetLastError());
+    std::swap(st, st_new);
     std::swap(w6[3], w6[4]);  // d1 <- d_new, d2 <- old d1
     std::swap(w6[0], w6[1]);  // v <- v_next, vp <- old v
     v = w6[0].get(); vp = w6[1].get(); d1 = w6[3].get(); d2 = w6[4].get();
@@ -464,13 +508,13 @@ static InnerResult cgls_run(dl_op* op, const double2* b, double2* x, double bnor
   double* pq = S.part.get();
   double* pr = S.part.get() + kMaxPartials;
   double* ps = S.part.get() + 2 * kMaxPartials;
+  int i_ss = S_SS, i_new = S_SS2;
   while (res.mvp < max_mvp) {
     apply_wilson(op, 0, p, q, 1, pq);
-    hipLaunchKernelGGL(k_fin_cgls_alpha, dim3(1), dim3(kBlock), 0, s, pq, nbw, S.sc.get());
-    hipLaunchKernelGGL(k_cgls_xr, dim3(nb), dim3(kBlock), 0, s, n, S.sc.get(), p, q, x, r, pr);
+    hipLaunchKernelGGL(k_cgls_step1, dim3(nb), dim3(kBlock), 0, s, n, pq, nbw, S.sc.get(), i_ss, p, q, x, r, pr);
     apply_wilson(op, 1, r, sv, 1, ps);
-    hipLaunchKernelGGL(k_fin_cgls_beta, dim3(1), dim3(kBlock), 0, s, ps, nbw, pr, nb, S.sc.get());
-    hipLaunchKernelGGL(k_xpay, dim3(G), dim3(kBlock), 0, s, n, S.sc.get(), (int)S_BETA, sv, p);
+    hipLaunchKernelGGL(k_cgls_step2, dim3(G), dim3(kBlock), 0, s, n, ps, nbw, pr, nb, S.sc.get(), i_ss, i_new, sv, p);
+    std::swap(i_ss, i_new);
     DL_HIP(hipGetLastError());
     res.mvp += 2;
     res.iters += 1;

@@ -11,8 +11,11 @@
 // every operator of a process makes the same choice and results are
 // reproducible within a run) and in a text cache file, one line per key:
 //
-//     <arch> <Lx>x<Ly>x<Lz>x<Lt> <prec> <nrhs> <variant> <order> <us>      (stencil)
+//     W21 <arch> <Lx>x<Ly>x<Lz>x<Lt> <prec> <nrhs> <variant> <order> <us>  (stencil)
 //     K <arch> <kind> <n> <nv> <nw> <grid> <tile> <us>                     (contraction)
+//
+// The stencil tag names the number of shapes that were compared, so a file written when there were
+// fewer is tuned again rather than believed.
 //
 // The file is $DEFLAN_TUNE_CACHE, else $HOME/.cache/deflan/tune.txt.
 // DEFLAN_AUTOTUNE=0 disables tuning (the default shapes are used).
@@ -66,6 +69,8 @@ std::string make_key(const std::string& arch, const Lattice& lat, int prec, int 
   return os.str();
 }
 
+std::string stencil_tag() { return "W" + std::to_string(kWilsonVariants); }
+
 void load_cache() {
   if (g_loaded) return;
   g_loaded = true;
@@ -88,7 +93,8 @@ void load_cache() {
     }
     int prec, nrhs, v, o;
     double us;
-    if (!(is >> arch >> dims >> prec >> nrhs >> v >> o >> us)) continue;
+    std::string tag;
+    if (!(is >> tag >> arch >> dims >> prec >> nrhs >> v >> o >> us) || tag != stencil_tag()) continue;
     if (v < 0 || v >= kWilsonVariants || o < 0 || o >= kWilsonOrders) continue;
     std::ostringstream k;
     k << arch << ' ' << dims << ' ' << prec << ' ' << nrhs;
@@ -111,7 +117,7 @@ void append_line(const std::string& text) {
 
 void append_cache(const std::string& key, const WilsonCfg& c, double us) {
   std::ostringstream os;
-  os << key << ' ' << c.variant << ' ' << c.order << ' ' << us;
+  os << stencil_tag() << ' ' << key << ' ' << c.variant << ' ' << c.order << ' ' << us;
   append_line(os.str());
 }
 

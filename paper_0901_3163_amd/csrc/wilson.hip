@@ -982,17 +982,122 @@ k_wilson_mr(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ i
   }
 }
 
+// One hop per wave: a block is one 64-site tile of one rhs and eight waves; wave h forms the
+// transported half spinor of hop h (x+, x-, y+, ...) for the tile's sites and leaves it in LDS, then
+// the block adds the eight hops in k_wilson's order, 12 components x 64 sites over 512 threads.  What
+// bounds a small lattice is the chain of memory latencies in a thread, not bytes: k_wilson walks four
+// pairs of hops one after the other, here every load of a site is in flight at once, on eight times as
+// many waves.  FP64, one field: 4^4 8.1 -> 5.0 us, 8^4 10.3 -> 5.9 us, 8^3 x 16 9.4 -> 5.8 us.
+// On larger lattices the LDS round trip costs more than it hides and the tuner takes other shapes.
+template <int MU, int S, class C>
+__device__ __forceinline__ void add_row(int spin, const C* g0, const C* g1, C& acc) {
+  // row `spin` of the rebuilt spinor from the half spinor (g0, g1), as in reconstruct()
+  if (spin == 0) acc = c_add(acc, *g0);
+  else if (spin == 1) acc = c_add(acc, *g1);
+  else if (spin == 2) {
+    if (MU == 0) acc = S > 0 ? c_sub(acc, c_i(*g1)) : c_add(acc, c_i(*g1));
+    if (MU == 1) acc = S > 0 ? c_add(acc, *g1) : c_sub(acc, *g1);
+    if (MU == 2) acc = S > 0 ? c_sub(acc, c_i(*g0)) : c_add(acc, c_i(*g0));
+    if (MU == 3) acc = S > 0 ? c_add(acc, *g0) : c_sub(acc, *g0);
+  } else {
+    if (MU == 0) acc = S > 0 ? c_sub(acc, c_i(*g0)) : c_add(acc, c_i(*g0));
+    if (MU == 1) acc = S > 0 ? c_sub(acc, *g0) : c_add(acc, *g0);
+    if (MU == 2) acc = S > 0 ? c_add(acc, c_i(*g1)) : c_sub(acc, c_i(*g1));
+    if (MU == 3) acc = S > 0 ? c_add(acc, *g1) : c_sub(acc, *g1);
+  }
+}
+
+template <class R, class SV, int WHICH, int RED>
+__global__ void __launch_bounds__(512)
+k_wilson_split(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ in, SV* __restrict__ out,
+               long fstride, int nrhs, double kappa, int Lx, int Ly, int Lz, int Lt, long V, long Vpad, int nbs,
+               int order, const double* __restrict__ scale, const int* __restrict__ active,
+               double* __restrict__ part) {
+  using C = typename CT<R>::type;
+  __shared__ C gs[8][6][kTile];
+  const int lb = order == 2 ? (int)blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
+  const int rhs = order == 1 ? lb / nbs : lb % nrhs;
+  const int sb = order == 1 ? lb % nbs : lb / nrhs;
+  if (active && !active[rhs]) return;
+  in += rhs * fstride;
+  out += rhs * fstride;
+  const int lane = threadIdx.x & 63, hop = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int site = sb * kTile + lane;
+  constexpr int SF = (WHICH == 1) ? 1 : -1;
+  if (site < V) {
+    const int mu = hop >> 1;
+    const bool fwd = (hop & 1) == 0;
+    const int st = mu == 0 ? 1 : mu == 1 ? Lx : mu == 2 ? Lx * Ly : Lx * Ly * Lz;
+    const int L = mu == 0 ? Lx : mu == 1 ? Ly : mu == 2 ? Lz : Lt;
+    const int x = (site / st) % L;
+    const int nb = fwd ? (x == L - 1 ? site - (L - 1) * st : site + st) : (x == 0 ? site + (L - 1) * st : site - st);
+    C p[12], h[6], g[6], u[9];
+    const SV* pp = in + sp_base(nb);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) p[c] = sld(pp + c * kTile);
+    const C* up = U + lk_base(fwd ? site : nb, mu);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) u[e] = up[e * kTile];
+    if (fwd) {
+      project_mu<SF>(mu, p, h);
+      mul_half<false>(u, h, g);
+    } else {
+      project_mu<-SF>(mu, p, h);
+      mul_half<true>(u, h, g);
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) gs[hop][c][lane] = g[c];
+  }
+  __syncthreads();
+  const R sc = scale ? (R)scale[rhs] : (R)1;
+  const R mk = (R)(-kappa);
+  double red = 0.0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int c = hop + 8 * k;  // component of this wave
+    if (c >= 12) break;
+    SV* op = out + sp_base(site) + c * kTile;
+    if (site >= V) {
+      if (site < Vpad) sst(op, CT<R>::make(0, 0));
+      continue;
+    }
+    const int spin = c / 3, a = c % 3;
+    C acc = CT<R>::make(0, 0);
+#define DL_ROW(H, MU, S) add_row<MU, S>(spin, &gs[H][a][lane], &gs[H][3 + a][lane], acc)
+    DL_ROW(0, 0, SF);
+    DL_ROW(1, 0, -SF);
+    DL_ROW(2, 1, SF);
+    DL_ROW(3, 1, -SF);
+    DL_ROW(4, 2, SF);
+    DL_ROW(5, 2, -SF);
+    DL_ROW(6, 3, SF);
+    DL_ROW(7, 3, -SF);
+#undef DL_ROW
+    const C p = sld(in + sp_base(site) + c * kTile);
+    C r = CT<R>::make(fma(mk, acc.x, p.x) * sc, fma(mk, acc.y, p.y) * sc);
+    if (WHICH == 2 && c >= 6) r = CT<R>::make(-r.x, -r.y);
+    sst(op, r);
+    if (RED == 1) red += (double)fma(r.x, r.x, r.y * r.y);
+    if (RED == 2) red += (double)fma(p.x, r.x, p.y * r.y) * sc;
+  }
+  if (RED != 0) {
+    __shared__ double lds[8];
+    const double s = block_sum<512>(red, lds);
+    if (threadIdx.x == 0) part[(long)rhs * nbs + sb] = s;
+  }
+}
+
 // Launch-shape variants.  0-3: k_wilson with (threads per block, occupancy hint)
 // {(256,2), (128,2), (512,1), (256,1)}; 4-6: k_wilson_tm, 256 threads per block, time
 // chunks of T = 4, 8, 16 slices; 7-10: k_wilson_tml with 64 sites per block and
 // (rhs per block, T) = (4, 8), (4, 16), (8, 8), (2, 8).
 // 15-17: k_wilson_mr with (threads per block, rhs per thread) = (256, 2), (256, 4), (128, 2).
 // 18-19: k_wilson_tmp with box blocks of whole x rows (T = 8, 16); where no box tiles the
-// slice they launch variants 12 and 13.
+// slice they launch variants 12 and 13.  20: k_wilson_split, 64 sites per block.
 static constexpr int kVariantNT[kWilsonVariants] = {256, 128, 512, 256, 256, 256, 256, 64, 64, 64, 64, 256, 256, 256, 256,
-                                                    256, 256, 128, 256, 256};
-static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16};
-static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 4, 2, 1, 1};
+                                                    256, 256, 128, 256, 256, 64};
+static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16, 0};
+static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1};
 
 static int tm_nb3(const Lattice& lat, int v) {
   return (lat.L[0] * lat.L[1] * lat.L[2] + kVariantNT[v] - 1) / kVariantNT[v];
@@ -1083,6 +1188,15 @@ static void launch_mr(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, dou
 }
 
 template <class R, class SV, int WHICH, int RED>
+static void launch_split(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, const SV* in, SV* out,
+                         long fstride, int nrhs, int order, const double* scale, const int* active, double* part,
+                         int nbs) {
+  const int* L = lat.L;
+  hipLaunchKernelGGL((k_wilson_split<R, SV, WHICH, RED>), dim3(nbs * nrhs), dim3(512), 0, s, U, in, out, fstride, nrhs,
+                     kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, nbs, order, scale, active, part);
+}
+
+template <class R, class SV, int WHICH, int RED>
 static void launch_variant(int variant, hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa,
                            const SV* in, SV* out, long fstride, int nrhs, int order,
                            const double* scale, const int* active, double* part, int nbs) {
@@ -1131,6 +1245,9 @@ static void launch_variant(int variant, hipStream_t s, const Lattice& lat, const
       break;
     case 17:
       launch_mr<R, SV, WHICH, RED, 128, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs);
+      break;
+    case 20:
+      launch_split<R, SV, WHICH, RED>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs);
       break;
     default: launch_one<R, SV, WHICH, RED, 256, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs); break;
   }

@@ -74,3 +74,40 @@ def test_layout_conversions_round_trip(gpu_ctx, dims, prec):
     z = op.apply_batched(0, {"f64": 0, "f32": 1, "bf16": 2}[prec], torch.from_numpy(x).cuda())
     assert np.array_equal(z.cpu().numpy(), y)
     op.close()
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (3, 5, 2, 4), (2, 2, 2, 2), (5, 7, 3, 11)])
+@pytest.mark.parametrize("order", [0, 1, 2])
+def test_hop_per_wave_stencil_bits(gpu_ctx, dims, order, monkeypatch):
+    """The one-hop-per-wave stencil (shape 20) adds the same terms in the same order as shape 0: the
+    same bits in every storage, M, M^dag and gamma5 M, on ragged tiles and extents of 2."""
+    from paper_0901_3163_amd import deflan
+    from lattice_inputs import su3_links
+    op = deflan.Operator(gpu_ctx, dims, su3_links(dims, 4), 0.131, deflan.DL_G5M)
+    psi = np.stack([gaussian_spinor(dims, 70 + i) for i in range(3)])
+    for prec in (0, 1, 2):
+        for which in (0, 1, 2):
+            monkeypatch.setenv("DEFLAN_WILSON_VARIANT", "0,0")
+            ref = op.apply_batched(which, prec, psi)
+            monkeypatch.setenv("DEFLAN_WILSON_VARIANT", f"20,{order}")
+            assert np.array_equal(op.apply_batched(which, prec, psi), ref), (prec, which)
+    op.close()
+
+
+@pytest.mark.parametrize("storage,kind", [("f64", "mdagm"), ("f64", "g5m"), ("f32", "mdagm"), ("bf16", "g5m")])
+def test_solves_on_hop_per_wave_stencil(gpu_ctx, storage, kind, monkeypatch):
+    """Its fused reductions: a later rhs converges to the oracle's residual on a ragged lattice."""
+    from paper_0901_3163_amd import deflan
+    from lattice_inputs import su3_links
+    dims = (5, 7, 3, 11)
+    U = su3_links(dims, 4)
+    ora = dirac.WilsonOperator(U, dims, 0.128)
+    op = deflan.Operator(gpu_ctx, dims, U, 0.128, deflan.DL_G5M if kind == "g5m" else deflan.DL_MDAGM)
+    B = np.stack([gaussian_spinor(dims, 80 + i) for i in range(2)])
+    monkeypatch.setenv("DEFLAN_WILSON_VARIANT", "20,0")
+    kw = dict() if storage == "f64" else dict(storage={"f32": 1, "bf16": 2}[storage], batched=1)
+    X, st, rc = op.solve_next(B, None, 1e-10, **kw)
+    assert rc == 0
+    for b, x in zip(B, X):
+        assert np.linalg.norm(b.ravel() - ora.M(x.ravel())) <= 1.0001e-10 * np.linalg.norm(b)
+    op.close()
