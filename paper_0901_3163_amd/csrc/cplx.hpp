@@ -88,6 +88,22 @@ __device__ __forceinline__ void sst(bf2* p, float2 v) {
   *reinterpret_cast<unsigned*>(p) = __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2_st));
 }
 
+// Non-temporal forms: for data that is not read again before the caches have turned over.
+typedef double f64x2_st __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void sst_nt(double2* p, double2 v) {
+  const f64x2_st t = {v.x, v.y};
+  __builtin_nontemporal_store(t, reinterpret_cast<f64x2_st*>(p));
+}
+__device__ __forceinline__ void sst_nt(float2* p, float2 v) {
+  const f32x2_st t = {v.x, v.y};
+  __builtin_nontemporal_store(t, reinterpret_cast<f32x2_st*>(p));
+}
+__device__ __forceinline__ void sst_nt(bf2* p, float2 v) {
+  const f32x2_st f = {v.x, v.y};
+  __builtin_nontemporal_store(__builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2_st)),
+                              reinterpret_cast<unsigned*>(p));
+}
+
 // Four consecutive storage elements (16 B of BF16, 32 B of FP32; the address a multiple of
 // four elements) widened to / rounded from FP32.
 __device__ __forceinline__ void sld4(const float2* p, float2* o) {

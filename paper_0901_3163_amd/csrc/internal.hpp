@@ -161,8 +161,9 @@ void pack_links(hipStream_t s, const Lattice& lat, const double2* host_layout, d
 // hop's link loaded once for the group.  18-19 = the slice-staged form with each block a box of
 // whole x rows spanning y and z (T = 8, 16), so z neighbours inside the box come from LDS too
 // (variants 12 and 13 where no box tiles the slice).  20 = one hop per wave, eight waves per 64 sites
-// (small lattices).
-constexpr int kWilsonVariants = 21;
+// (small lattices).  21-26 = boxes of whole x rows marching through T = 4, 8, 16 slices, for one (21-23) or
+// two rhs (24-26) a block.
+constexpr int kWilsonVariants = 27;
 constexpr int kWilsonOrders = 3;
 struct WilsonCfg {
   int variant = 0;

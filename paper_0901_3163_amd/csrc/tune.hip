@@ -11,7 +11,7 @@
 // every operator of a process makes the same choice and results are
 // reproducible within a run) and in a text cache file, one line per key:
 //
-//     W21 <arch> <Lx>x<Ly>x<Lz>x<Lt> <prec> <nrhs> <variant> <order> <us>  (stencil)
+//     W27 <arch> <Lx>x<Ly>x<Lz>x<Lt> <prec> <nrhs> <variant> <order> <us>  (stencil)
 //     K <arch> <kind> <n> <nv> <nw> <grid> <tile> <us>                     (contraction)
 //
 // The stencil tag names the number of shapes that were compared, so a file written when there were

@@ -1087,6 +1087,262 @@ k_wilson_split(const typename CT<R>::type* __restrict__ U, const SV* __restrict_
   }
 }
 
+// Box form: a block is a box of by x bz whole x rows of a time slice (at most NT sites, spare threads
+// idle) that marches through a time chunk for RT right-hand sides.  Each slice's centre spinors sit
+// widened in LDS, so x neighbours (and y and z neighbours inside the box) are read from there, the
+// others from memory; the t hops are carried along t as in k_wilson_tm.  Every hop is unrolled
+// with its own projection, one link is loaded ahead of the hop before it, and serves the RT rhs.
+// What bounds it: FP32 instruction issue (packed FP32 arithmetic is not used), 8 hops x 108 operations
+// and the epilogue, about 1050 a site and rhs or 224 us for 64 rhs of 16^3 x 32, and below that the latency
+// of its loads: two rhs a thread halve the link loads and give two chains at two waves per SIMD.
+// 16^3 x 32, 64 BF16 rhs: 438 -> 341 us alone (2.5 TB/s algorithmic; 458 -> 374 within D-CG); 16 FP32 rhs
+// 178 -> 103 (187 -> 171 within D-CG, where its input comes from HBM); FP64, one field 35 -> 30, 64 rhs
+// 1237 -> 957; 24^3 x 48 FP64, one field 167 -> 133 (4.8 TB/s).  Without the spinors one hop ahead 64 BF16
+// rhs take 393 us.
+// nt: the result is stored non-temporally.  RES, LO: the residual forms of k_wilson_tm.
+template <class R, class SV, int WHICH, int RED, int RT, int NT, bool RES = false, int LO = 0>
+__global__ void __launch_bounds__(NT, RT == 1 && sizeof(R) == 4 ? 3 : 2)
+k_wilson_box(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ in, SV* __restrict__ out,
+             long fstride, int nrhs, double kappa, int Lx, int Ly, int Lz, int Lt, long V, long Vpad, int T, int nb3,
+             int nbs, int ngroups, int order, const double* __restrict__ scale, const int* __restrict__ active,
+             double* __restrict__ part, int boy, int boz, int nt, const SV* __restrict__ add,
+             void* __restrict__ lo) {
+  using C = typename CT<R>::type;
+  static_assert(!RES || RT == 1, "the residual is formed for one rhs a block");
+  __shared__ C ps[RT][12 * NT];
+  const int lb = order == 2 ? (int)blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
+  const int rg = order == 1 ? lb / nbs : lb % ngroups;
+  const int sb = order == 1 ? lb % nbs : lb / ngroups;
+  bool on[RT];
+  bool any = false;
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const int r = rg * RT + j;
+    on[j] = r < nrhs && (!active || active[r]);
+    any |= on[j];
+  }
+  if (!any) {  // uniform over the block
+    if (RES && RED != 0 && threadIdx.x == 0) part[(long)rg * nbs + sb] = 0.0;  // an inactive rhs sums to 0
+    return;
+  }
+  in += (long)rg * RT * fstride;
+  if (LO == 0) out += (long)rg * RT * fstride;
+  if (RES) add += (long)rg * fstride;
+  float2* lo32 = LO == 1 ? static_cast<float2*>(lo) + (long)rg * fstride : nullptr;
+  bf2* lo16 = LO == 2 ? static_cast<bf2*>(lo) + (long)rg * fstride : nullptr;
+  const int b3 = sb % nb3, tc = sb / nb3;
+  const int V3 = Lx * Ly * Lz;
+  const int tid = (int)threadIdx.x;
+  const bool valid = tid < Lx * boy * boz;
+  const int nby = Ly / boy;
+  const int x = tid % Lx, ly = (tid / Lx) % boy, lz = tid / (Lx * boy);
+  const int y = (b3 % nby) * boy + ly, z = (b3 / nby) * boz + lz;
+  const int s3 = x + Lx * (y + Ly * z);
+  const int t0 = tc * T;
+  const int t1 = t0 + T < Lt ? t0 + T : Lt;
+  double red[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) red[j] = 0.0;
+  // (the low-precision residual's padding sites are zero already and stay so)
+  if (LO == 0 && b3 == 0 && t1 == Lt) {
+    for (long sp = V + tid; sp < Vpad; sp += NT)
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+        if (on[j]) {
+          SV* op = out + j * fstride + sp_base((int)sp);
+#pragma unroll
+          for (int c = 0; c < 12; ++c) sst(op + c * kTile, CT<R>::make(0, 0));
+        }
+  }
+  // site offsets of the neighbours, and their LDS index (-1: outside the box)
+  const int sy = Lx, sz = Lx * Ly;
+  const int fx = x == Lx - 1 ? 1 - Lx : 1, bx = x == 0 ? Lx - 1 : -1;
+  const int fy = y == Ly - 1 ? (1 - Ly) * sy : sy, by = y == 0 ? (Ly - 1) * sy : -sy;
+  const int fz = z == Lz - 1 ? (1 - Lz) * sz : sz, bz = z == 0 ? (Lz - 1) * sz : -sz;
+  const int ry = Lx, rz = Lx * boy;
+  const int lfy = ly < boy - 1 ? tid + ry : boy == Ly ? tid - (boy - 1) * ry : -1;
+  const int lby = ly > 0 ? tid - ry : boy == Ly ? tid + (boy - 1) * ry : -1;
+  const int lfz = lz < boz - 1 ? tid + rz : boz == Lz ? tid - (boz - 1) * rz : -1;
+  const int lbz = lz > 0 ? tid - rz : boz == Lz ? tid + (boz - 1) * rz : -1;
+  constexpr int SF = (WHICH == 1) ? 1 : -1;
+  constexpr bool PF = sizeof(R) == 4;  // spinors one hop ahead (FP64 has no registers left for them)
+  const R mk = (R)(-kappa);
+  R sc[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) sc[j] = scale && on[j] ? (R)scale[rg * RT + j] : (R)1;
+  // Loads at a uniform base and a 32-bit byte offset of the site (links and fields are under 4 GB
+  // here), with the components in the instruction's offset, counted from the middle one.
+  auto link = [&](unsigned site, int mu) {
+    Lk<C> l;
+    const char* base = reinterpret_cast<const char*>(U + (mu * 9 + 4) * kTile);
+    const unsigned o = (site >> 6) * (unsigned)(kLinkC * kTile * sizeof(C)) + (site & 63) * (unsigned)sizeof(C);
+#pragma unroll
+    for (int e = 0; e < 9; ++e)
+      l.e[e] = *reinterpret_cast<const C*>(base + o + (e - 4) * (int)(kTile * sizeof(C)));
+    return l;
+  };
+  auto soff = [](unsigned site) {
+    return (site >> 6) * (unsigned)(kSpin * kTile * sizeof(SV)) + (site & 63) * (unsigned)sizeof(SV);
+  };
+  auto spinor = [&](int j, unsigned site) {
+    SpRaw<SV> r;
+    const char* base = reinterpret_cast<const char*>(in + j * fstride + 6 * kTile);
+    const unsigned o = soff(site);
+#pragma unroll
+    for (int c = 0; c < 12; ++c)
+      r.e[c] = *reinterpret_cast<const SV*>(base + o + (c - 6) * (int)(kTile * sizeof(SV)));
+    return r;
+  };
+  SpRaw<SV> cur[RT];  // centre spinors of the slice, as stored
+  Lk<C> u;            // link of the next hop
+  C gb[RT][6];        // backward t hop into the slice
+  if (valid) {
+    const int sprev = (t0 == 0 ? Lt - 1 : t0 - 1) * V3 + s3;
+    u = link(sprev, 3);
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+      if (!on[j]) continue;
+      const SpRaw<SV> raw = spinor(j, sprev);
+      cur[j] = spinor(j, t0 * V3 + s3);
+      C p[12], h[6];
+#pragma unroll
+      for (int c = 0; c < 12; ++c) p[c] = sldv(raw.e[c]);
+      project<3, -SF>(p, h);
+      mul_half<true>(u.e, h, gb[j]);
+    }
+    u = link(t0 * V3 + s3, 0);
+  }
+#pragma unroll 1
+  for (int t = t0; t < t1; ++t) {
+    int site = t * V3 + s3;
+    asm volatile("" : "+v"(site));  // keeps the compiler from carrying one pointer per hop around the loop
+    __syncthreads();  // the previous slice is no longer read from LDS
+    if (valid) {
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) ps[j][c * NT + tid] = sldv(cur[j].e[c]);
+    }
+    __syncthreads();
+    if (!valid) continue;
+    C acc[RT][12];
+    SpRaw<SV> raw[RT];
+    // One hop: the next hop's link and, where they lie outside the box, its spinors are requested first
+    // (nli, nnb: their LDS index and site), then this one's are taken from LDS (index li >= 0; x
+    // neighbours always are) or from the registers that the hop before filled.
+    auto hop = [&](auto MUc, auto Sc, auto DAGc, int li, int nb, auto FIRSTc, int next_site, int next_mu, int nli,
+                   int nnb) {
+      constexpr int MU = decltype(MUc)::value, S = decltype(Sc)::value;
+      constexpr bool DAG = decltype(DAGc)::value, FIRST = decltype(FIRSTc)::value;
+      // opaque here, so that the loads of later hops are not gathered ahead of this one's arithmetic
+      asm volatile("" : "+v"(next_site), "+v"(nnb));
+      const Lk<C> un = link(next_site, next_mu);
+#pragma unroll
+      for (int j = 0; j < RT; ++j) {
+        if (!on[j]) continue;
+        C p[12], h[6], g[6];
+        if (MU == 0 || li >= 0) {
+#pragma unroll
+          for (int c = 0; c < 12; ++c) p[c] = ps[j][c * NT + li];
+        } else {
+          if (!PF) raw[j] = spinor(j, nb);
+#pragma unroll
+          for (int c = 0; c < 12; ++c) p[c] = sldv(raw[j].e[c]);
+        }
+        if (PF && !(MU == 0 && FIRST) && nli < 0) raw[j] = spinor(j, nnb);
+        project<MU, S>(p, h);
+        mul_half<DAG>(u.e, h, g);
+        if (FIRST) {
+#pragma unroll
+          for (int c = 0; c < 12; ++c) acc[j][c] = CT<R>::make(0, 0);
+        }
+        reconstruct<MU, S>(acc[j], g);
+        // the sums are wanted here: left to itself the compiler sinks a hop's arithmetic to the slice's
+        // end, with every hop's operands held (256 registers)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[j][c].x), "+v"(acc[j][c].y));
+      }
+      u = un;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr std::integral_constant<int, SF> P{};
+    constexpr std::integral_constant<int, -SF> N{};
+    constexpr std::integral_constant<int, 0> X{};
+    constexpr std::integral_constant<int, 1> Y{};
+    constexpr std::integral_constant<int, 2> Z{};
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    const int snext = (t == Lt - 1 ? 0 : t + 1) * V3 + s3;
+    if (!PF) u = link(site, 0);
+    hop(X, P, no, tid + fx, site, yes, site + bx, 0, 0, site);
+    hop(X, N, yes, tid + bx, site, no, site, 1, lfy, site + fy);
+    hop(Y, P, no, lfy, site + fy, no, site + by, 1, lby, site + by);
+    hop(Y, N, yes, lby, site + by, no, site, 2, lfz, site + fz);
+    hop(Z, P, no, lfz, site + fz, no, site + bz, 2, lbz, site + bz);
+    hop(Z, N, yes, lbz, site + bz, no, site, 3, -1, snext);
+    Lk<C> ux{};
+    if (PF) ux = link(snext, 0);  // the next slice's first link
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+      if (!on[j]) continue;
+      cur[j] = PF ? raw[j] : spinor(j, snext);
+      C p[12], h[6], g[6];
+#pragma unroll
+      for (int c = 0; c < 12; ++c) p[c] = sldv(cur[j].e[c]);
+      project<3, SF>(p, h);
+      mul_half<false>(u.e, h, g);
+      reconstruct<3, SF>(acc[j], g);
+      reconstruct<3, -SF>(acc[j], gb[j]);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) p[c] = ps[j][c * NT + tid];
+      project<3, -SF>(p, h);
+      mul_half<true>(u.e, h, gb[j]);
+      char* op = reinterpret_cast<char*>(out + j * fstride + 6 * kTile);
+      const unsigned oo = soff(site);
+      R sred = 0;  // this site's share of the reduction, summed in R
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        const int co = (c - 6) * (int)(kTile * sizeof(SV));
+        C r = CT<R>::make(fma(mk, acc[j][c].x, p[c].x) * sc[j], fma(mk, acc[j][c].y, p[c].y) * sc[j]);
+        if (WHICH == 2 && c >= 6) r = CT<R>::make(-r.x, -r.y);
+        if (RES) {
+          const C bv = sldv(*reinterpret_cast<const SV*>(reinterpret_cast<const char*>(add + 6 * kTile) + oo + co));
+          r = CT<R>::make(bv.x - r.x, bv.y - r.y);
+        }
+        if (LO != 0) {
+          const float2 vf = make_float2((float)r.x, (float)r.y);
+          float2 vs = vf;  // the stored value, as read back
+          if (LO == 1) {
+            sst_nt(lo32 + sp_base(site) + c * kTile, vf);
+          } else {
+            sst_nt(lo16 + sp_base(site) + c * kTile, vf);
+            vs = make_float2(__uint_as_float((unsigned)f2bf(vf.x) << 16), __uint_as_float((unsigned)f2bf(vf.y) << 16));
+          }
+          r = CT<R>::make((R)vs.x, (R)vs.y);
+        } else if (nt) {
+          sst_nt(reinterpret_cast<SV*>(op + oo + co), r);
+        } else {
+          sst(reinterpret_cast<SV*>(op + oo + co), r);
+        }
+        if (RED == 1) sred = fma(r.x, r.x, fma(r.y, r.y, sred));
+        if (RED == 2) sred = fma(p[c].x, r.x, fma(p[c].y, r.y, sred));
+      }
+      if (RED == 1) red[j] += (double)sred;
+      if (RED == 2) red[j] += (double)sred * sc[j];
+    }
+    if (PF) u = ux;
+  }
+  if (RED != 0) {
+    __shared__ double lds[NT / 64];
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+      if (!on[j]) continue;  // uniform over the block
+      const double s = block_sum<NT>(red[j], lds);
+      if (tid == 0) part[(long)(rg * RT + j) * nbs + sb] = s;
+    }
+  }
+}
+
 // Launch-shape variants.  0-3: k_wilson with (threads per block, occupancy hint)
 // {(256,2), (128,2), (512,1), (256,1)}; 4-6: k_wilson_tm, 256 threads per block, time
 // chunks of T = 4, 8, 16 slices; 7-10: k_wilson_tml with 64 sites per block and
@@ -1094,12 +1350,25 @@ k_wilson_split(const typename CT<R>::type* __restrict__ U, const SV* __restrict_
 // 15-17: k_wilson_mr with (threads per block, rhs per thread) = (256, 2), (256, 4), (128, 2).
 // 18-19: k_wilson_tmp with box blocks of whole x rows (T = 8, 16); where no box tiles the
 // slice they launch variants 12 and 13.  20: k_wilson_split, 64 sites per block.
+// 21-26: k_wilson_box with (rhs per block, T) = (1, 4), (1, 8), (1, 16), (2, 4), (2, 8), (2, 16) (FP64: one rhs
+// per block); where no box fits a slice they launch variants 4 to 6.
 static constexpr int kVariantNT[kWilsonVariants] = {256, 128, 512, 256, 256, 256, 256, 64, 64, 64, 64, 256, 256, 256, 256,
-                                                    256, 256, 128, 256, 256, 64};
-static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16, 0};
-static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1};
+                                                    256, 256, 128, 256, 256, 64, 256, 256, 256, 256, 256, 256};
+static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16, 0,
+                                                   4, 8, 16, 4, 8, 16};
+static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1,
+                                                    1, 1, 1, 2, 2, 2};
+constexpr int kFirstBox = 21, kBoxNT = 256;
 
+static bool site_box(const Lattice& lat, int* by, int* bz);
+
+// Blocks of a time slice.
 static int tm_nb3(const Lattice& lat, int v) {
+  if (v >= kFirstBox) {
+    int by = 1, bz = 1;
+    site_box(lat, &by, &bz);
+    return (lat.L[1] / by) * (lat.L[2] / bz);
+  }
   return (lat.L[0] * lat.L[1] * lat.L[2] + kVariantNT[v] - 1) / kVariantNT[v];
 }
 static int tm_chunks(const Lattice& lat, int v) { return (lat.L[3] + kVariantT[v] - 1) / kVariantT[v]; }
@@ -1146,6 +1415,58 @@ static bool tmp_box(const Lattice& lat, int nt, int* by, int* bz) {
     }
   }
   return found;
+}
+
+// Box of k_wilson_box: by | Ly, bz | Lz, Lx by bz <= NT, for the least work per site: neighbour spinors from
+// memory (2 / by and 2 / bz a site unless the box spans the lattice) on top of about five spinors'
+// worth of arithmetic, over the share of threads with a site.  False if no box fills half a block.
+static bool site_box(const Lattice& lat, int* by, int* bz) {
+  const int* L = lat.L;
+  double best = 1e300;
+  for (int y = 1; y <= L[1] && L[0] * y <= kBoxNT; ++y) {
+    if (L[1] % y != 0) continue;
+    for (int z = 1; z <= L[2] && L[0] * y * z <= kBoxNT; ++z) {
+      if (L[2] % z != 0 || 2 * L[0] * y * z < kBoxNT) continue;
+      const double far = (y < L[1] ? 2.0 / y : 0.0) + (z < L[2] ? 2.0 / z : 0.0);
+      const double cost = (5.0 + far) / (L[0] * y * z);
+      if (cost < best) {
+        best = cost;
+        *by = y;
+        *bz = z;
+      }
+    }
+  }
+  return best < 1e300;
+}
+
+// The launch shape that variant v runs on this lattice: k_wilson_box needs a box, 32-bit byte offsets (the
+// FP64 links under 4 GB) and no more blocks a field than the fused reductions take.
+static int effective_variant(const Lattice& lat, int v) {
+  int by, bz;
+  if (v < kFirstBox) return v;
+  if ((double)lat.ntiles * kTile * kLinkC * sizeof(double2) < 4294967296.0 && site_box(lat, &by, &bz) &&
+      (long)(lat.L[1] / by) * (lat.L[2] / bz) * ((lat.L[3] + kVariantT[v] - 1) / kVariantT[v]) <= kMaxPartials)
+    return v;
+  return 4 + (v - kFirstBox) % 3;
+}
+
+// Inputs and results that together exceed the 256 MB Infinity Cache: storing the result past it leaves
+// the inputs there (12 FP32 rhs of 16^3 x 32 108 -> 85 us, 64 BF16 rhs 352 -> 341 us); a smaller result is
+// kept for the kernel that reads it next.
+static int stream_out(long fstride, int nrhs, size_t elem) { return 2.0 * nrhs * fstride * elem > 256e6; }
+
+template <class R, class SV, int WHICH, int RED, int RT>
+static void launch_box(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, const SV* in, SV* out,
+                       long fstride, int nrhs, int order, const double* scale, const int* active, double* part,
+                       int nbs, int v) {
+  const int* L = lat.L;
+  int by = 1, bz = 1;
+  site_box(lat, &by, &bz);
+  const int ngroups = (nrhs + RT - 1) / RT;
+  hipLaunchKernelGGL((k_wilson_box<R, SV, WHICH, RED, RT, kBoxNT>), dim3(nbs * ngroups), dim3(kBoxNT), 0, s, U, in, out,
+                     fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v],
+                     tm_nb3(lat, v), nbs, ngroups, order, scale, active, part, by, bz, stream_out(fstride, nrhs, sizeof(SV)),
+                     static_cast<const SV*>(nullptr), static_cast<void*>(nullptr));
 }
 
 template <class R, class SV, int WHICH, int RED, int NT, bool LK, bool PF, bool BOX = false>
@@ -1245,6 +1566,15 @@ static void launch_variant(int variant, hipStream_t s, const Lattice& lat, const
       break;
     case 17:
       launch_mr<R, SV, WHICH, RED, 128, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs);
+      break;
+    case 24: case 25: case 26:
+      if constexpr (sizeof(R) == 4) {
+        launch_box<R, SV, WHICH, RED, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
+        break;
+      }
+      [[fallthrough]];
+    case 21: case 22: case 23:
+      launch_box<R, SV, WHICH, RED, 1>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
       break;
     case 20:
       launch_split<R, SV, WHICH, RED>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs);
@@ -1489,18 +1819,28 @@ int wilson_residual_f64(hipStream_t s, const Lattice& lat, const double2* U, dou
                         void* lo, int lo_prec) {
   if (lat.eo) fail(DL_E_INVALID, "the fused residual serves whole-lattice operators");
   if ((lo == nullptr) == (r == nullptr)) fail(DL_E_INVALID, "the fused residual goes to r or to lo");
-  constexpr int v = 6;  // time-marching, 256 threads, chunks of 16 slices
+  // k_wilson_box with one rhs a block and chunks of 16 slices, in hardware block order (16^3 x 32, 64 rhs:
+  // 1283 us by k_wilson_tm, 1122 here; chunks of 4 and 8 within 1% of it); k_wilson_tm where it has no box
+  const int v = effective_variant(lat, kFirstBox + 2);
   const int nbs = tm_nb3(lat, v) * tm_chunks(lat, v);
   if (nbs > kMaxPartials) fail(DL_E_INVALID, "lattice too large for fused reduction");
   if ((long)nbs * nrhs > 2147483647L) fail(DL_E_INVALID, "grid too large");
   const int* L = lat.L;
+  int by = 1, bz = 1;
+  if (v >= kFirstBox) site_box(lat, &by, &bz);
 #define DL_RES(LOP)                                                                                                 \
-  hipLaunchKernelGGL((k_wilson_tm<double, double2, 0, 1, 256, true, LOP>), dim3(nbs * nrhs), dim3(256), 0, s, U, x,  \
-                     r, fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v],       \
-                     tm_nb3(lat, v), nbs, 2, static_cast<const double*>(nullptr), active, part, b, lo)
-  if (!lo) DL_RES(0);
-  else if (lo_prec == DL_FP32) DL_RES(1);
-  else if (lo_prec == DL_BF16) DL_RES(2);
+  if (v >= kFirstBox)                                                                                               \
+    hipLaunchKernelGGL((k_wilson_box<double, double2, 0, 1, 1, kBoxNT, true, LOP>), dim3(nbs * nrhs), dim3(kBoxNT),  \
+                       0, s, U, x, r, fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile,       \
+                       kVariantT[v], tm_nb3(lat, v), nbs, nrhs, 2, static_cast<const double*>(nullptr), active,      \
+                       part, by, bz, stream_out(fstride, nrhs, sizeof(double2)), b, lo);                             \
+  else                                                                                                              \
+    hipLaunchKernelGGL((k_wilson_tm<double, double2, 0, 1, 256, true, LOP>), dim3(nbs * nrhs), dim3(256), 0, s, U,   \
+                       x, r, fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v],  \
+                       tm_nb3(lat, v), nbs, 2, static_cast<const double*>(nullptr), active, part, b, lo)
+  if (!lo) { DL_RES(0); }
+  else if (lo_prec == DL_FP32) { DL_RES(1); }
+  else if (lo_prec == DL_BF16) { DL_RES(2); }
   else fail(DL_E_INVALID, "lo_prec must be DL_FP32 or DL_BF16");
 #undef DL_RES
   DL_HIP(hipGetLastError());
@@ -1509,7 +1849,7 @@ int wilson_residual_f64(hipStream_t s, const Lattice& lat, const double2* U, dou
 
 int wilson_nbs(const Lattice& lat, const WilsonCfg& cfg) {
   if (lat.eo) return (int)((lat.V + 255) / 256);
-  const int v = cfg.variant % kWilsonVariants;
+  const int v = effective_variant(lat, cfg.variant % kWilsonVariants);
   if (kVariantT[v] > 0) return tm_nb3(lat, v) * tm_chunks(lat, v);
   const int nt = kVariantNT[v];
   return (int)((lat.V + nt - 1) / nt);
@@ -1526,10 +1866,10 @@ int wilson_batched(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double
                    const SV* in, SV* out, long fstride, int nrhs, int red, const double* scale,
                    const int* active, double* part, WilsonCfg cfg) {
   if (lat.eo) return wilson_eo<R, SV>(s, lat, U, kappa, which, in, out, fstride, nrhs, red, scale, active, part);
-  const int v = cfg.variant % kWilsonVariants;
+  const int v = effective_variant(lat, cfg.variant % kWilsonVariants);
   const int nbs = wilson_nbs(lat, cfg);
   if (red && nbs > kMaxPartials) fail(DL_E_INVALID, "lattice too large for fused reduction");
-  if ((long)nbs * ((nrhs + kVariantRT[v] - 1) / kVariantRT[v]) > 2147483647L) fail(DL_E_INVALID, "grid too large");
+  if ((long)nbs * nrhs > 2147483647L && (long)nbs * ((nrhs + kVariantRT[v] - 1) / kVariantRT[v]) > 2147483647L) fail(DL_E_INVALID, "grid too large");
   const int o = cfg.order;
 #define DL_W(WH, RD) launch_variant<R, SV, WH, RD>(v, s, lat, U, kappa, in, out, fstride, nrhs, o, scale, active, part, nbs)
   if (which == 0) { if (red == 0) DL_W(0, 0); else if (red == 1) DL_W(0, 1); else DL_W(0, 2); }

@@ -111,3 +111,46 @@ def test_solves_on_hop_per_wave_stencil(gpu_ctx, storage, kind, monkeypatch):
     for b, x in zip(B, X):
         assert np.linalg.norm(b.ravel() - ora.M(x.ravel())) <= 1.0001e-10 * np.linalg.norm(b)
     op.close()
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 2, 5), (8, 8, 8, 16), (24, 8, 2, 17), (5, 9, 6, 3), (32, 16, 4, 4),
+                                  (256, 2, 2, 2), (7, 11, 2, 9), (3, 5, 7, 6)])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_box_stencil_bits(gpu_ctx, dims, nrhs, monkeypatch):
+    """The box stencils (shapes 21 to 26) against shape 0, bit for bit: boxes that fill a block or
+    leave threads idle, y and z faces inside and outside the box, whole planes, ragged time chunks,
+    an odd number of rhs for two a block, lattices without a box (the last falls back)."""
+    from paper_0901_3163_amd import deflan
+    from lattice_inputs import su3_links
+    op = deflan.Operator(gpu_ctx, dims, su3_links(dims, 4), 0.131, deflan.DL_G5M)
+    psi = np.stack([gaussian_spinor(dims, 70 + i) for i in range(nrhs)])
+    for prec in (0, 1, 2):
+        for which in (0, 1, 2):
+            monkeypatch.setenv("DEFLAN_WILSON_VARIANT", "0,0")
+            ref = op.apply_batched(which, prec, psi)
+            for v in range(21, 27):
+                monkeypatch.setenv("DEFLAN_WILSON_VARIANT", f"{v},{(v + which) % 3}")
+                assert np.array_equal(op.apply_batched(which, prec, psi), ref), (prec, which, v)
+    op.close()
+
+
+@pytest.mark.parametrize("variant", [21, 23, 24, 26])
+@pytest.mark.parametrize("storage,kind", [("f64", "mdagm"), ("f32", "mdagm"), ("bf16", "mdagm"), ("bf16", "g5m")])
+def test_solves_on_box_stencil(gpu_ctx, storage, kind, variant, monkeypatch):
+    """Their fused reductions and the residual form (FP32 and BF16 reliable updates), with a zero rhs
+    whose blocks are masked: every rhs meets the oracle's residual."""
+    from paper_0901_3163_amd import deflan
+    from lattice_inputs import su3_links
+    dims = (8, 12, 4, 6)
+    U = su3_links(dims, 4)
+    ora = dirac.WilsonOperator(U, dims, 0.128)
+    op = deflan.Operator(gpu_ctx, dims, U, 0.128, deflan.DL_G5M if kind == "g5m" else deflan.DL_MDAGM)
+    B = np.stack([gaussian_spinor(dims, 80 + i) for i in range(5)])
+    B[1] = 0.0
+    monkeypatch.setenv("DEFLAN_WILSON_VARIANT", f"{variant},0")
+    kw = dict() if storage == "f64" else dict(storage={"f32": 1, "bf16": 2}[storage], batched=1)
+    X, st, rc = op.solve_next(B, None, 1e-10, **kw)
+    assert rc == 0 and not X[1].any()
+    for b, x in zip(B, X):
+        assert np.linalg.norm(b.ravel() - ora.M(x.ravel())) <= 1.0001e-10 * np.linalg.norm(b)
+    op.close()
