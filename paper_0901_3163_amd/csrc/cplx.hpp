@@ -104,6 +104,15 @@ __device__ __forceinline__ void sst_nt(bf2* p, float2 v) {
                               reinterpret_cast<unsigned*>(p));
 }
 
+__device__ __forceinline__ float2 sld_nt(const float2* p) {
+  const f32x2_st t = __builtin_nontemporal_load(reinterpret_cast<const f32x2_st*>(p));
+  return make_float2(t.x, t.y);
+}
+__device__ __forceinline__ float2 sld_nt(const bf2* p) {
+  const unsigned w = __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p));
+  return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xFFFF0000u));
+}
+
 // Four consecutive storage elements (16 B of BF16, 32 B of FP32; the address a multiple of
 // four elements) widened to / rounded from FP32.
 __device__ __forceinline__ void sld4(const float2* p, float2* o) {
@@ -127,6 +136,8 @@ __device__ __forceinline__ void sst4(float2* p, const float2* v) {
   reinterpret_cast<float4*>(p)[0] = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
   reinterpret_cast<float4*>(p)[1] = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
 }
+typedef unsigned u32x4_st __attribute__((ext_vector_type(4)));
+typedef float f32x4_st __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ unsigned bf_pack(float2 v) {
   const f32x2_st f = {v.x, v.y};
   return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2_st));
@@ -134,6 +145,46 @@ __device__ __forceinline__ unsigned bf_pack(float2 v) {
 __device__ __forceinline__ void sst4(bf2* p, const float2* v) {
   *reinterpret_cast<uint4*>(p) = make_uint4(bf_pack(v[0]), bf_pack(v[1]), bf_pack(v[2]), bf_pack(v[3]));
 }
+
+// The elements of one 16-byte access (2 FP32, 4 BF16), NT: past the caches.
+template <class SV>
+struct Vec16;
+template <>
+struct Vec16<float2> {
+  static constexpr int N = 2;
+  template <bool NT>
+  __device__ static __forceinline__ void load(const float2* p, float2* o) {
+    const f32x4_st* q = reinterpret_cast<const f32x4_st*>(p);
+    const f32x4_st a = NT ? __builtin_nontemporal_load(q) : *q;
+    o[0] = make_float2(a.x, a.y);
+    o[1] = make_float2(a.z, a.w);
+  }
+  template <bool NT>
+  __device__ static __forceinline__ void store(float2* p, const float2* v) {
+    const f32x4_st a = {v[0].x, v[0].y, v[1].x, v[1].y};
+    if (NT) __builtin_nontemporal_store(a, reinterpret_cast<f32x4_st*>(p));
+    else *reinterpret_cast<f32x4_st*>(p) = a;
+  }
+};
+template <>
+struct Vec16<bf2> {
+  static constexpr int N = 4;
+  template <bool NT>
+  __device__ static __forceinline__ void load(const bf2* p, float2* o) {
+    const u32x4_st* q = reinterpret_cast<const u32x4_st*>(p);
+    const u32x4_st u = NT ? __builtin_nontemporal_load(q) : *q;
+    o[0] = bf_word(u.x);
+    o[1] = bf_word(u.y);
+    o[2] = bf_word(u.z);
+    o[3] = bf_word(u.w);
+  }
+  template <bool NT>
+  __device__ static __forceinline__ void store(bf2* p, const float2* v) {
+    const u32x4_st u = {bf_pack(v[0]), bf_pack(v[1]), bf_pack(v[2]), bf_pack(v[3])};
+    if (NT) __builtin_nontemporal_store(u, reinterpret_cast<u32x4_st*>(p));
+    else *reinterpret_cast<u32x4_st*>(p) = u;
+  }
+};
 
 template <class R> struct CT;
 template <> struct CT<double> {

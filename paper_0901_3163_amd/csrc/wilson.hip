@@ -1319,13 +1319,20 @@ k_wilson_box(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
             vs = make_float2(__uint_as_float((unsigned)f2bf(vf.x) << 16), __uint_as_float((unsigned)f2bf(vf.y) << 16));
           }
           r = CT<R>::make((R)vs.x, (R)vs.y);
-        } else if (nt) {
-          sst_nt(reinterpret_cast<SV*>(op + oo + co), r);
-        } else {
-          sst(reinterpret_cast<SV*>(op + oo + co), r);
         }
+        acc[j][c] = r;
         if (RED == 1) sred = fma(r.x, r.x, fma(r.y, r.y, sred));
         if (RED == 2) sred = fma(p[c].x, r.x, fma(p[c].y, r.y, sred));
+      }
+      if (LO == 0) {
+        char* o = op + oo - 6 * (int)(kTile * sizeof(SV));
+        if (nt) {
+#pragma unroll
+          for (int c = 0; c < 12; ++c) sst_nt(reinterpret_cast<SV*>(o) + c * kTile, acc[j][c]);
+        } else {
+#pragma unroll
+          for (int c = 0; c < 12; ++c) sst(reinterpret_cast<SV*>(o) + c * kTile, acc[j][c]);
+        }
       }
       if (RED == 1) red[j] += (double)sred;
       if (RED == 2) red[j] += (double)sred * sc[j];
