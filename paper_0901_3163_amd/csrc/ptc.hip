@@ -14,7 +14,7 @@
 // Backward pass: the adjoint of T_h is T_{-h} and channel mixing commutes with the
 // transport, so the data gradient is the forward kernel with W'_{-h} = W_h^H.  The
 // weight gradient G_W[h][o][i] = sum_x sum_c G_out[o](x)_c conj((T_h in[i])(x)_c)
-// is accumulated per 64-site chunk from LDS in FP64 and reduced in a fixed order.
+// is accumulated per 64-site chunk from LDS in FP64 (on the matrix cores) and reduced in a fixed order.
 #include "ptc.hpp"
 #include "small.hpp"
 #include "tsk.hpp"
@@ -63,70 +63,106 @@ __device__ __forceinline__ void transport3(const float2 u[9], bool fwd, const fl
   }
 }
 
-// One network layer over `gridDim.y` fields: thread = site.  W ([9][COUT][CIN]) is staged in LDS.
-// NONLIN: out = f(z), z saved to zsave if given; else out = out_scale[item] * z (out_scale may be NULL).
-template <int CIN, int COUT, bool NONLIN>
+// One network layer over `gridDim.y` fields: thread = site.
+// ACT 1: out = f(z), z saved to zsave if given;
+// 2 (backward): out = the gradient G_z behind the non-linearity, from the sum G_f and z = zsave,
+// G_z = g G_f + 2 g' Re<G_f, z> z with g(s) = (1 + s)^-1/2, s = |z|^2 (a pass over G of its own took
+// 348 us for 16 channels of 8 fields of 16^3 x 32).
+// The weights are the same for every lane, so they come through the scalar cache and are SGPR operands.
+// Bound by the vector FMAs: 8 fields of 16^3 x 32 16 -> 16 1.16 -> 0.99 ms (0.96 of it issue), 4 -> 16 0.35 -> 0.33
+// (0.29); the weights in LDS and each channel's loads waited for took the difference.
+template <int CIN, int COUT, int ACT>
 __global__ void __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(CIN == 4 ? 2 : 3, CIN == 4 ? 2 : 3)))
 k_ptc_layer(const float2* __restrict__ U, const float2* __restrict__ in, float2* __restrict__ out,
             float2* __restrict__ zsave, const float2* __restrict__ W, int Lx, int Ly, int Lz, int Lt, int V,
-            int Vpad, long in_stride, long out_stride, const double* __restrict__ out_scale) {
-  __shared__ float2 ws[9 * COUT * CIN];
-  for (int e = threadIdx.x; e < 9 * COUT * CIN; e += blockDim.x) ws[e] = W[e];
-  __syncthreads();
-  const int item = blockIdx.y;
+            int Vpad, int nblk, long in_stride, long out_stride) {
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int item = lb / nblk;
   in += item * in_stride;
   out += item * out_stride;
   if (zsave) zsave += item * out_stride;
-  const int site = blockIdx.x * blockDim.x + threadIdx.x;
+  const int site = (lb - item * nblk) * blockDim.x + threadIdx.x;
   if (site >= Vpad) return;
   if (site >= V) {  // padding sites stay zero
     for (int o = 0; o < COUT; ++o)
       for (int c = 0; c < 3; ++c) {
         out[act_idx(site, COUT, o, c)] = make_float2(0.f, 0.f);
-        if (zsave) zsave[act_idx(site, COUT, o, c)] = make_float2(0.f, 0.f);
+        if (ACT == 1 && zsave) zsave[act_idx(site, COUT, o, c)] = make_float2(0.f, 0.f);
       }
     return;
   }
+  // CB channels at a time: transported, then the next CB channels' loads (and the next hop's link) are
+  // issued and stay in flight while these are mixed into the COUT sums
+  constexpr int CB = CIN == 4 ? 4 : 2, NB = CIN / CB;
   float2 acc[COUT][3];
 #pragma unroll
   for (int o = 0; o < COUT; ++o)
 #pragma unroll
     for (int c = 0; c < 3; ++c) acc[o][c] = make_float2(0.f, 0.f);
+  int nb = site;
+  float2 u[9], a[CB][3];
+  auto load = [&](int ch0) {
+#pragma unroll
+    for (int i = 0; i < CB; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a[i][c] = in[act_idx(nb, CIN, ch0 + i, c)];
+  };
+  load(0);
+#pragma unroll
+  for (int e = 0; e < 9; ++e) u[e] = make_float2(0.f, 0.f);
 #pragma unroll 1
-  for (int h = 0; h < 9; ++h) {
-    int nb = site, mu = 0;
-    bool fwd = true;
-    float2 u[9];
-    if (h > 0) {
-      hop_geom(h, site, Lx, Ly, Lz, Lt, nb, mu, fwd);
-      const int ls = fwd ? site : nb;
+  for (int st = 0; st < 9 * NB; ++st) {
+    const int h = st / NB, k = st % NB;
+    float2 tr[CB][3];
+    if (h == 0) {
+#pragma unroll
+      for (int i = 0; i < CB; ++i)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tr[i][c] = a[i][c];
+    } else {
+#pragma unroll
+      for (int i = 0; i < CB; ++i) transport3(u, (h & 1) != 0, a[i], tr[i]);
+    }
+    if (k + 1 < NB) {
+      load((k + 1) * CB);
+    } else if (h < 8) {
+      int mu;
+      bool f;
+      hop_geom(h + 1, site, Lx, Ly, Lz, Lt, nb, mu, f);
+      const int ls = f ? site : nb;
 #pragma unroll
       for (int e = 0; e < 9; ++e) u[e] = U[lnk_idx(ls, mu, e)];
+      load(0);
     }
-    const float2* wh = ws + h * COUT * CIN;
-#pragma unroll 2
-    for (int i = 0; i < CIN; ++i) {
-      float2 a[3], tr[3];
+    __builtin_amdgcn_sched_barrier(0);
+    const float2* wh = W + h * COUT * CIN + k * CB;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) a[c] = in[act_idx(nb, CIN, i, c)];
-      if (h == 0) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) tr[c] = a[c];
-      } else {
-        transport3(u, fwd, a, tr);
-      }
+    for (int i = 0; i < CB; ++i)
 #pragma unroll
       for (int o = 0; o < COUT; ++o) {
         const float2 w = wh[o * CIN + i];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) acc[o][c] = c_fma(w, tr[c], acc[o][c]);
+        for (int c = 0; c < 3; ++c) acc[o][c] = c_fma(w, tr[i][c], acc[o][c]);
       }
-    }
   }
-  const float sc = out_scale ? (float)out_scale[item] : 1.f;
 #pragma unroll
   for (int o = 0; o < COUT; ++o) {
-    if (NONLIN) {
+    if (ACT == 2) {
+      float2 z[3];
+      float n2 = 0.f, re = 0.f;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        z[c] = zsave[act_idx(site, COUT, o, c)];
+        n2 += z[c].x * z[c].x + z[c].y * z[c].y;
+        re += acc[o][c].x * z[c].x + acc[o][c].y * z[c].y;
+      }
+      const float gf = 1.f / sqrtf(1.f + n2);
+      const float dgf = -0.5f * gf * gf * gf;
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        out[act_idx(site, COUT, o, c)] = c_axpy(2.f * dgf * re, z[c], c_scale(acc[o][c], gf));
+    } else {
       float n2 = 0.f;
 #pragma unroll
       for (int c = 0; c < 3; ++c) n2 += acc[o][c].x * acc[o][c].x + acc[o][c].y * acc[o][c].y;
@@ -136,33 +172,115 @@ k_ptc_layer(const float2* __restrict__ U, const float2* __restrict__ in, float2*
         if (zsave) zsave[act_idx(site, COUT, o, c)] = acc[o][c];
         out[act_idx(site, COUT, o, c)] = c_scale(acc[o][c], g);
       }
-    } else {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) out[act_idx(site, COUT, o, c)] = c_scale(acc[o][c], sc);
     }
   }
 }
 
+// The 16 -> 4 layer: two waves per tile of 64 sites.  Each transports eight of the input channels, they
+// meet in LDS, and each mixes them into two of the outputs (out = out_scale[item] * z; out_scale may be
+// NULL), in the same order as one thread per site would.  Bound by what misses the L2: a site is read nine
+// times, and with one site per thread an XCD's 32 CUs held 32 * 1024 sites of 384 B, three times its 4 MB,
+// so that 90 % of the reads went past it (7.4 TB/s).  Two waves per tile keep as many waves on fewer
+// sites: 16 fields of 16^3 x 32 1158 -> 870 us, of which the vector FMAs are 650 (one thread per site with
+// its loads ahead 1018, one or two such waves per SIMD 1240 and 1018; four or five blocks a CU 1000 and 1040).
+__global__ void __launch_bounds__(128)
+k_ptc_layer16_4(const float2* __restrict__ U, const float2* __restrict__ in, float2* __restrict__ out,
+                const float2* __restrict__ W, int Lx, int Ly, int Lz, int Lt, int V, int ntiles, long in_stride,
+                long out_stride, const double* __restrict__ out_scale) {
+  __shared__ float2 tl[48][64];  // [3 channel + colour][site]
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int item = lb / ntiles, tile = lb - item * ntiles;
+  in += item * in_stride;
+  out += item * out_stride;
+  const int site = min(tile * 64 + lane, V - 1);  // a padding site repeats the last one
+  float2 acc[2][3];
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[o][c] = make_float2(0.f, 0.f);
+  float2 u[9], a[8][3];
+  auto load = [&](int h) {
+    int nb = site;
+    if (h > 0) {
+      int mu;
+      bool f;
+      hop_geom(h, site, Lx, Ly, Lz, Lt, nb, mu, f);
+      const int ls = f ? site : nb;
+#pragma unroll
+      for (int e = 0; e < 9; ++e) u[e] = U[lnk_idx(ls, mu, e)];
+    }
+    const float2* ap = in + act_idx(nb, 16, 8 * w, 0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a[i][c] = ap[(3 * i + c) * kTile];
+  };
+#pragma unroll
+  for (int e = 0; e < 9; ++e) u[e] = make_float2(0.f, 0.f);
+  load(0);
+#pragma unroll 1
+  for (int h = 0; h < 9; ++h) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float2 tr[3];
+      if (h == 0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tr[c] = a[i][c];
+      } else {
+        transport3(u, (h & 1) != 0, a[i], tr);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) tl[3 * (8 * w + i) + c][lane] = tr[c];
+    }
+    if (h < 8) load(h + 1);  // in flight during the mixing
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    const float2* wh = W + h * 64 + 32 * w;
+#pragma unroll 8
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float2 t = tl[3 * i + c][lane];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) acc[o][c] = c_fma(wh[o * 16 + i], t, acc[o][c]);
+      }
+    __syncthreads();
+  }
+  const float sc = out_scale ? (float)out_scale[item] : 1.f;
+  const bool ok = tile * 64 + lane < V;
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      out[act_idx(tile * 64 + lane, 4, 2 * w + o, c)] = ok ? c_scale(acc[o][c], sc) : make_float2(0.f, 0.f);
+}
+
 // ---- 16 -> 16 layer with BF16 channel mixing on the matrix cores (inference) ------------------
 //
-// Per wave: one tile of 64 sites.  For each hop the wave transports its 16 input channels (FP32,
+// Two waves per tile of 64 sites.  For each hop each wave transports 8 of the input channels (FP32,
 // one thread per site), rounds them to BF16 and stages them in LDS; the channel mixing is then
 // the real form of a complex product: with K = (channel i, re/im) interleaved (32 per hop) and
 // rows m < 16 the real parts, m >= 16 the imaginary parts of the 16 output channels,
 //     A[o][2i] = Re W, A[o][2i+1] = -Im W, A[16+o][2i] = Im W, A[16+o][2i+1] = Re W,
 // and out[m][(site, colour)] += sum_k A[m][k] T[k][(site, colour)] on v_mfma_f32_32x32x16_bf16:
-// six 32-column tiles (3 colours x 2 halves of the tile's sites) and two K-steps per hop, FP32
+// six 32-column tiles (3 colours x 2 halves of the tile's sites, one half a wave) and two K-steps per hop, FP32
 // accumulation over all nine hops.  Lane l supplies row / column l % 32 and K-slice 8 * (l / 32)
 // of both operands; the result register j of lane l is row 8 (j / 4) + 4 (l / 32) + j % 4, so a
 // lane holds the real and imaginary parts of 8 output channels for the 3 colours of two sites,
 // which is all the per-channel non-linearity needs.
+// Bound by the latency of the loads and the vector work of the transport (16 fields of 16^3 x 32: 0.47 ms of
+// issue; the products 0.05).  Two waves share a tile and the next hop's loads are in flight during the products:
+// 1509 -> 917 us.  One wave per tile with its loads ahead took 1041, with 62M L2 misses (7.7 TB/s) against 29M.
 typedef __bf16 bf16x8_n __attribute__((ext_vector_type(8)));
 typedef float f32x16_n __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4_n __attribute__((ext_vector_type(4)));
 typedef float f32x2_n __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_n __attribute__((ext_vector_type(2)));
 
-constexpr int kMixRow = 40;  // BF16 entries per (colour, site) row of the LDS stage (32 used; 80 B keeps 16 B alignment)
+// BF16 entries per (colour, site) row of the LDS stage; its four 16 B parts are swapped by bits 2-3 of the
+// site against bank conflicts
+constexpr int kMixRow = 32;
 
 __device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
   const f32x2_n f = {a, b};
@@ -191,127 +309,102 @@ __global__ void k_ptc_wfrag16(const float2* __restrict__ W, u32x4_n* __restrict_
 }
 
 template <bool NONLIN>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(128)
 k_ptc_layer16_mfma(const float2* __restrict__ U, const float2* __restrict__ in, float2* __restrict__ out,
                    const u32x4_n* __restrict__ frag, int Lx, int Ly, int Lz, int Lt, int V, int ntiles,
                    long in_stride, long out_stride, const double* __restrict__ out_scale) {
-  __shared__ unsigned short stage[4][3][64 * kMixRow];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int tile = blockIdx.x * 4 + wid;
-  const int item = blockIdx.y;
-  if (tile >= ntiles) return;  // whole waves only: no barrier below spans waves
+  __shared__ __align__(16) unsigned short stage[2][3 * 64 * kMixRow];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int item = lb / ntiles, tile = lb - item * ntiles;
   in += item * in_stride;
   out += item * out_stride;
-  const int site = tile * 64 + lane;
-  const bool valid = site < V;
-  unsigned short* st = &stage[wid][0][0];
-  f32x16_n acc[6];
+  const int site = min(tile * 64 + lane, V - 1);  // a padding site repeats the last one (columns do not mix)
+  f32x16_n acc[3];
 #pragma unroll
-  for (int q = 0; q < 6; ++q)
+  for (int q = 0; q < 3; ++q)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[q][j] = 0.f;
   const int g = lane >> 5, col = lane & 31;
-#pragma unroll 1
-  for (int h = 0; h < 9; ++h) {
-    int nb = site, mu = 0;
-    bool fwd = true;
-    float2 u[9];
-    if (valid && h > 0) {
-      hop_geom(h, site, Lx, Ly, Lz, Lt, nb, mu, fwd);
-      const int ls = fwd ? site : nb;
+  float2 u[9], a[8][3];
+  auto load = [&](int h) {
+    int nb = site;
+    if (h > 0) {
+      int mu;
+      bool f;
+      hop_geom(h, site, Lx, Ly, Lz, Lt, nb, mu, f);
+      const int ls = f ? site : nb;
 #pragma unroll
       for (int e = 0; e < 9; ++e) u[e] = U[lnk_idx(ls, mu, e)];
     }
-    // transport the 16 channels of this site's neighbour, BF16 into the stage [colour][site][k]
-#pragma unroll 2
-    for (int i = 0; i < 16; ++i) {
-      float2 a[3], tr[3];
-      if (valid) {
+    const float2* ap = in + act_idx(nb, 16, 8 * w, 0);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) a[c] = in[act_idx(nb, 16, i, c)];
-        if (h == 0) {
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-          for (int c = 0; c < 3; ++c) tr[c] = a[c];
-        } else {
-          transport3(u, fwd, a, tr);
-        }
+      for (int c = 0; c < 3; ++c) a[i][c] = ap[(3 * i + c) * kTile];
+  };
+#pragma unroll
+  for (int e = 0; e < 9; ++e) u[e] = make_float2(0.f, 0.f);
+  load(0);
+#pragma unroll 1
+  for (int h = 0; h < 9; ++h) {
+    unsigned short* st = stage[h & 1];
+    const u32x4_n af[2] = {frag[h * 128 + lane], frag[h * 128 + 64 + lane]};
+    unsigned pk[3][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float2 tr[3];
+      if (h == 0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tr[c] = a[i][c];
       } else {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) tr[c] = make_float2(0.f, 0.f);
+        transport3(u, (h & 1) != 0, a[i], tr);
       }
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        *reinterpret_cast<unsigned*>(st + (c * 64 + lane) * kMixRow + 2 * i) = pack_bf16x2(tr[c].x, tr[c].y);
+      for (int c = 0; c < 3; ++c) pk[c][i] = pack_bf16x2(tr[c].x, tr[c].y);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const u32x4_n af = frag[(h * 2 + ks) * 64 + lane];
+    for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
+      for (int q = 0; q < 2; ++q)
+        *reinterpret_cast<u32x4_n*>(st + (c * 64 + lane) * kMixRow + 8 * ((2 * w + q) ^ ((lane >> 2) & 3))) =
+            u32x4_n{pk[c][4 * q], pk[c][4 * q + 1], pk[c][4 * q + 2], pk[c][4 * q + 3]};
+    if (h < 8) load(h + 1);  // in flight during the products
+    __syncthreads();         // one per hop: the other half of `stage` was read before the last one
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const u32x4_n bf = *reinterpret_cast<const u32x4_n*>(st + (c * 64 + half * 32 + col) * kMixRow + 16 * ks +
-                                                               8 * g);
-          acc[c * 2 + half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8_n, af), __builtin_bit_cast(bf16x8_n, bf), acc[c * 2 + half], 0, 0, 0);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const u32x4_n bf = *reinterpret_cast<const u32x4_n*>(st + (c * 64 + w * 32 + col) * kMixRow +
+                                                             8 * ((2 * ks + g) ^ ((col >> 2) & 3)));
+        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_n, af[ks]),
+                                                         __builtin_bit_cast(bf16x8_n, bf), acc[c], 0, 0, 0);
+      }
   }
-  // epilogue: lane holds rows 8q + 4g + r (q, r < 4) of the six tiles: channel o = 8 (q % 2) + 4g + r,
+  // epilogue: lane holds rows 8q + 4g + r (q, r < 4) of the wave's three tiles: channel o = 8 (q % 2) + 4g + r,
   // real part for q < 2, imaginary part (row 16 + o) for q >= 2
   const float sc = out_scale ? (float)out_scale[item] : 1.f;
+  const int s2 = tile * 64 + w * 32 + col;
+  const bool ok = s2 < V;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int s2 = tile * 64 + half * 32 + col;
-    const bool ok = s2 < V;
+  for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int r = 0; r < 4; ++r) {
+      const int o = 8 * q + 4 * g + r;
+      float2 z[3];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int o = 8 * q + 4 * g + r;
-        float2 z[3];
+      for (int c = 0; c < 3; ++c) z[c] = make_float2(acc[c][4 * q + r], acc[c][4 * (q + 2) + r]);
+      float gsc = sc;
+      if (NONLIN) {
+        float n2 = 0.f;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) z[c] = make_float2(acc[c * 2 + half][4 * q + r], acc[c * 2 + half][4 * (q + 2) + r]);
-        float gsc = sc;
-        if (NONLIN) {
-          float n2 = 0.f;
-#pragma unroll
-          for (int c = 0; c < 3; ++c) n2 += z[c].x * z[c].x + z[c].y * z[c].y;
-          gsc = 1.f / sqrtf(1.f + n2);
-        }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) out[act_idx(s2, 16, o, c)] = ok ? c_scale(z[c], gsc) : make_float2(0.f, 0.f);
+        for (int c = 0; c < 3; ++c) n2 += z[c].x * z[c].x + z[c].y * z[c].y;
+        gsc = 1.f / sqrtf(1.f + n2);
       }
-  }
-}
-
-// Backward of f: G_z = g G_f + 2 g' Re<G_f, z> z with g(s) = (1 + s)^-1/2, s = |z|^2 (in place on G).
-__global__ void k_ptc_nonlin_bwd(const float2* __restrict__ zs, float2* __restrict__ G, int C, int V, long stride) {
-  const int item = blockIdx.y;
-  zs += item * stride;
-  G += item * stride;
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;  // (site, channel)
-  if (idx >= (long)V * C) return;
-  const int site = (int)(idx / C), ch = (int)(idx % C);
-  float2 z[3], g[3];
-  float n2 = 0.f, re = 0.f;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    z[c] = zs[act_idx(site, C, ch, c)];
-    g[c] = G[act_idx(site, C, ch, c)];
-    n2 += z[c].x * z[c].x + z[c].y * z[c].y;
-    re += g[c].x * z[c].x + g[c].y * z[c].y;
-  }
-  const float gf = 1.f / sqrtf(1.f + n2);
-  const float dgf = -0.5f * gf * gf * gf;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) G[act_idx(site, C, ch, c)] = c_axpy(2.f * dgf * re, z[c], c_scale(g[c], gf));
+      for (int c = 0; c < 3; ++c) out[act_idx(s2, 16, o, c)] = ok ? c_scale(z[c], gsc) : make_float2(0.f, 0.f);
+    }
 }
 
 // Adjoint weights of a [9][cout][cin] layer: Wt[rev(h)][i][o] = conj(W[h][o][i]).
@@ -324,82 +417,177 @@ __global__ void k_ptc_adjoint_weights(const float2* __restrict__ W, float2* __re
   Wt[((long)rh * cin + i) * cout + o] = make_float2(w.x, -w.y);
 }
 
-// Weight-gradient partials: block (chunk group, hop h, item); thread p = (o, i) for p < COUT*CIN.
-// The block walks chunks blockIdx.x, blockIdx.x + gridDim.x, ... staging the transported inputs
-// and output gradients of each 64-site chunk in LDS.  part layout:
-//   part[((item * 9 + h) * COUT * CIN + p) * 2 * gridDim.x + {block (re), gridDim.x + block (im)}]
+// Weight-gradient partials: block (chunk group, hop h, item), four waves.  The block walks 64-site
+// chunks blockIdx.x, blockIdx.x + gridDim.x, ... staging the transported inputs a and the output
+// gradients g of a chunk in LDS (one wave per channel, lane = site: coalesced loads, the link read
+// once per wave), and contracts them over (site, colour) on the FP64 matrix cores: rows are the real
+// and imaginary parts of g's channels, columns those of a's, so a lane's one LDS read per operand gives
+// a real and an imaginary row (column), and each wave takes a quarter of the 192 products.  Then
+// G = sum g conj(a) is Re = <g_re, a_re> + <g_im, a_im>, Im = <g_im, a_re> - <g_re, a_im>.  Products of
+// two FP32 numbers are exact in FP64 and summed in FP64, as before.  Bound by the FP64 matrix rate
+// and the vector instructions around it, which do not overlap with FP64 matrix products (16 -> 16, 8 fields of
+// 16^3 x 32: 0.74 + 0.35 ms); with vector FMAs, a conversion per operand and gathered loads it took 3.69 ms,
+// now 1.35 (16 -> 4: 2.05 -> 0.80, 4 -> 16: 1.67 -> 0.74).  The nine hops of a chunk range are neighbours on one
+// XCD, where they read the same g and a through its L2, and the next chunk's loads are in flight during
+// the products (1.82 ms without these two).
+// part layout: part[((item * 9 + h) * COUT * CIN + p) * 2 * gridDim.x + {block (re), gridDim.x + block (im)}]
+typedef double f64x4_n __attribute__((ext_vector_type(4)));
+
 template <int CIN, int COUT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 3)
 k_ptc_wgrad(const float2* __restrict__ U, const float2* __restrict__ in, const float2* __restrict__ G, int Lx,
-            int Ly, int Lz, int Lt, int V, int nchunks, long in_stride, long g_stride, double* __restrict__ part) {
-  __shared__ float2 tl[64][CIN][3];
-  __shared__ float2 gl[64][COUT][3];
-  const int h = blockIdx.y, item = blockIdx.z;
+            int Ly, int Lz, int Lt, int V, int nchunks, int nblk, long in_stride, long g_stride,
+            double* __restrict__ part) {
+  constexpr int RI = CIN + 1, RO = COUT + 1;        // LDS rows, padded
+  constexpr int CA = CIN / 4, CG = COUT / 4;        // channels a wave stages
+  constexpr int NR = COUT == 16 ? 2 : 1;            // row tiles: re and im apart, or both in one
+  constexpr int NC = CIN == 16 ? 2 : 1;             // column tiles
+  __shared__ __align__(16) char smem[192 * (RI + RO) * sizeof(float2)];
+  float2* tl = reinterpret_cast<float2*>(smem);     // [colour * 64 + site][channel]
+  float2* gl = tl + 192 * RI;
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int h = lb % 9, blk = (lb / 9) % nblk, item = lb / (9 * nblk);
   in += item * in_stride;
   G += item * g_stride;
-  const int p = threadIdx.x;
-  const int o = p / CIN, i = p % CIN;
-  double re = 0.0, im = 0.0;
-  for (int chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
-    for (int e = threadIdx.x; e < 64 * CIN; e += blockDim.x) {
-      const int ls = e / CIN, ci = e % CIN;
-      const int site = chunk * 64 + ls;
-      float2 tr[3] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
-      if (site < V) {
-        int nb = site, mu = 0;
-        bool fwd = true;
-        if (h > 0) hop_geom(h, site, Lx, Ly, Lz, Lt, nb, mu, fwd);
-        float2 a[3];
-        for (int c = 0; c < 3; ++c) a[c] = in[act_idx(nb, CIN, ci, c)];
-        if (h == 0) {
-          for (int c = 0; c < 3; ++c) tr[c] = a[c];
-        } else {
-          float2 u[9];
-          const int lsite = fwd ? site : nb;
-          for (int q = 0; q < 9; ++q) u[q] = U[lnk_idx(lsite, mu, q)];
-          transport3(u, fwd, a, tr);
-        }
-      }
-      for (int c = 0; c < 3; ++c) tl[ls][ci][c] = tr[c];
-    }
-    for (int e = threadIdx.x; e < 64 * COUT; e += blockDim.x) {
-      const int ls = e / COUT, co = e % COUT;
-      const int site = chunk * 64 + ls;
-      for (int c = 0; c < 3; ++c) gl[ls][co][c] = site < V ? G[act_idx(site, COUT, co, c)] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    if (p < COUT * CIN) {
-      for (int ls = 0; ls < 64; ++ls)
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int rc = lane & 15, kq = lane >> 4;         // row / column and k of this lane's operands
+  f64x4_n acc[NR][NC];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const float2 g = gl[ls][o][c], a = tl[ls][i][c];
-          re += (double)g.x * a.x + (double)g.y * a.y;  // g * conj(a)
-          im += (double)g.y * a.x - (double)g.x * a.y;
-        }
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[r][c] = f64x4_n{0.0, 0.0, 0.0, 0.0};
+  float2 u[9], a[CA][3], gr[CG][3];
+  auto load = [&](int chunk) {
+    const int site = min(chunk * 64 + lane, V - 1);
+    int nb = site;
+    if (h > 0) {
+      int mu;
+      bool f;
+      hop_geom(h, site, Lx, Ly, Lz, Lt, nb, mu, f);
+      const int ls = f ? site : nb;
+#pragma unroll
+      for (int e = 0; e < 9; ++e) u[e] = U[lnk_idx(ls, mu, e)];
+    }
+    const float2* ap = in + act_idx(nb, CIN, wid, 0);
+    const float2* gp = G + act_idx(site, COUT, wid, 0);
+#pragma unroll
+    for (int k = 0; k < CA; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a[k][c] = ap[(12 * k + c) * kTile];
+#pragma unroll
+    for (int k = 0; k < CG; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) gr[k][c] = gp[(12 * k + c) * kTile];
+    if (chunk * 64 + 64 > V && chunk * 64 + lane >= V) {  // padding sites add nothing
+#pragma unroll
+      for (int k = 0; k < CA; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[k][c] = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < CG; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gr[k][c] = make_float2(0.f, 0.f);
+    }
+  };
+  // a lane's operands of k-step 0; with 4 channels rows (columns) 0..3 are real, 4..7 imaginary parts
+  // and 8..15 repeat them (not read at the end)
+  const float2* gq = reinterpret_cast<const float2*>(reinterpret_cast<const float*>(gl + kq * RO + (NR == 2 ? rc : rc & 3)) +
+                                                     (NR == 2 ? 0 : (rc >> 2) & 1));
+  const float2* aq = reinterpret_cast<const float2*>(reinterpret_cast<const float*>(tl + kq * RI + (NC == 2 ? rc : rc & 3)) +
+                                                     (NC == 2 ? 0 : (rc >> 2) & 1));
+  const int c1 = (int)((long)(blk + 1) * nchunks / nblk);
+  int chunk = (int)((long)blk * nchunks / nblk);
+#pragma unroll
+  for (int e = 0; e < 9; ++e) u[e] = make_float2(0.f, 0.f);
+  if (chunk < c1) load(chunk);
+  for (; chunk < c1; ++chunk) {
+#pragma unroll
+    for (int k = 0; k < CA; ++k) {
+      float2 tr[3];
+      if (h > 0) {
+        transport3(u, (h & 1) != 0, a[k], tr);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tr[c] = a[k][c];
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) tl[(c * 64 + lane) * RI + wid + 4 * k] = tr[c];
+    }
+#pragma unroll
+    for (int k = 0; k < CG; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) gl[(c * 64 + lane) * RO + wid + 4 * k] = gr[k][c];
+    __syncthreads();
+    if (chunk + 1 < c1) load(chunk + 1);
+    __builtin_amdgcn_sched_barrier(0);  // keep these loads ahead of the products
+#pragma unroll 4
+    for (int s = 0; s < 12; ++s) {
+      const int k = wid * 48 + 4 * s;
+      double A[NR], B[NC];
+      if (NR == 2) {
+        const float2 v = gq[k * RO];
+        A[0] = v.x;
+        A[NR - 1] = v.y;
+      } else {
+        A[0] = reinterpret_cast<const float*>(gq)[2 * k * RO];
+      }
+      if (NC == 2) {
+        const float2 v = aq[k * RI];
+        B[0] = v.x;
+        B[NC - 1] = v.y;
+      } else {
+        B[0] = reinterpret_cast<const float*>(aq)[2 * k * RI];
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[r], B[c], acc[r][c], 0, 0, 0);
     }
     __syncthreads();
   }
+  // add the four waves' tiles (register q of lane l is row 4 q + l / 16, column l % 16)
+  double* red = reinterpret_cast<double*>(smem);
+  static_assert(sizeof(smem) >= 4 * NR * NC * 256 * sizeof(double), "reduction buffer");
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) red[((wid * NR + r) * NC + c) * 256 + (4 * q + kq) * 16 + rc] = acc[r][c][q];
+  __syncthreads();
+  const int p = threadIdx.x;
   if (p < COUT * CIN) {
-    const long base = (((long)item * 9 + h) * COUT * CIN + p) * 2 * gridDim.x;
-    part[base + blockIdx.x] = re;
-    part[base + gridDim.x + blockIdx.x] = im;
+    const int o = p / CIN, i = p % CIN;
+    auto at = [&](int gi, int ai) {  // <g part gi, a part ai> of the pair, 0 real, 1 imaginary
+      const int rt = NR == 2 ? gi : 0, ct = NC == 2 ? ai : 0;
+      const int row = NR == 2 ? o : o + 4 * gi, col = NC == 2 ? i : i + 4 * ai;
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v += red[((w * NR + rt) * NC + ct) * 256 + row * 16 + col];
+      return v;
+    };
+    const long base = (((long)item * 9 + h) * COUT * CIN + p) * 2 * nblk;
+    part[base + blk] = at(0, 0) + at(1, 1);
+    part[base + nblk + blk] = at(1, 0) - at(0, 1);
   }
 }
 
-// grad[e] = sum over items and blocks of the partials of entry e = (h, o, i), fixed order.
-__global__ void k_ptc_wgrad_reduce(const double* __restrict__ part, int nitems, int nentries, int nblk,
-                                   float2* __restrict__ grad) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+// grad[e] = sum over items and blocks of the partials of entry e = (h, o, i), one wave per entry, fixed order.
+__global__ void __launch_bounds__(256)
+k_ptc_wgrad_reduce(const double* __restrict__ part, int nitems, int nentries, int nblk, float2* __restrict__ grad) {
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (e >= nentries) return;
   double re = 0.0, im = 0.0;
   for (int it = 0; it < nitems; ++it) {
     const long base = ((long)it * nentries + e) * 2 * nblk;
-    for (int c = 0; c < nblk; ++c) {
+    for (int c = lane; c < nblk; c += 64) {
       re += part[base + c];
       im += part[base + nblk + c];
     }
   }
-  grad[e] = make_float2((float)re, (float)im);
+  re = wave_sum(re);
+  im = wave_sum(im);
+  if (lane == 0) grad[e] = make_float2((float)re, (float)im);
 }
 
 // Adam with bias correction on each real component.
@@ -509,22 +697,23 @@ constexpr int kWgradBlocks = 64;    // chunk groups of the weight-gradient kerne
 long act_len(const Lattice& lat, int C) { return lat.ntiles * kTile * C * 3; }
 
 void launch_layer(hipStream_t s, const Lattice& lat, const float2* U, const float2* in, float2* out, float2* zsave,
-                  const float2* W, int cin, int cout, bool nonlin, int nitems, const double* out_scale) {
-  const int Vpad = (int)(lat.ntiles * kTile);
-  const dim3 grid((unsigned)((Vpad + 255) / 256), nitems), block(256);
+                  const float2* W, int cin, int cout, int act, int nitems, const double* out_scale) {
+  const int Vpad = (int)(lat.ntiles * kTile), nblk = (Vpad + 255) / 256;
+  const dim3 grid((unsigned)nblk * nitems), block(256);
   const int* L = lat.L;
   const long is = act_len(lat, cin), os = act_len(lat, cout);
   const int V = (int)lat.V;
 #define DL_LAYER(CI, CO, NL)                                                                                  \
   hipLaunchKernelGGL((k_ptc_layer<CI, CO, NL>), grid, block, 0, s, U, in, out, zsave, W, L[0], L[1], L[2], L[3], \
-                     V, Vpad, is, os, out_scale)
-  if (cin == 4 && cout == 16) {
-    if (nonlin) DL_LAYER(4, 16, true); else DL_LAYER(4, 16, false);
-  } else if (cin == 16 && cout == 16) {
-    if (nonlin) DL_LAYER(16, 16, true); else DL_LAYER(16, 16, false);
-  } else if (cin == 16 && cout == 4) {
-    if (nonlin) DL_LAYER(16, 4, true); else DL_LAYER(16, 4, false);
-  } else {
+                     V, Vpad, nblk, is, os)
+  if (cin == 4 && cout == 16 && act == 1) DL_LAYER(4, 16, 1);
+  else if (cin == 4 && cout == 16 && act == 2) DL_LAYER(4, 16, 2);
+  else if (cin == 16 && cout == 16 && act == 1) DL_LAYER(16, 16, 1);
+  else if (cin == 16 && cout == 16 && act == 2) DL_LAYER(16, 16, 2);
+  else if (cin == 16 && cout == 4 && act == 0)
+    hipLaunchKernelGGL(k_ptc_layer16_4, dim3((unsigned)lat.ntiles * nitems), dim3(128), 0, s, U, in, out, W, L[0], L[1],
+                       L[2], L[3], V, (int)lat.ntiles, is, os, out_scale);
+  else {
     fail(DL_E_INVALID, "unsupported layer width");
   }
 #undef DL_LAYER
@@ -535,21 +724,21 @@ void launch_layer(hipStream_t s, const Lattice& lat, const float2* U, const floa
 void layer_wgrad(hipStream_t s, const Lattice& lat, const float2* U, const float2* in, const float2* g, int cin,
                  int cout, int nitems, double* part, float2* G) {
   const int nblk = (int)std::min<long>(lat.ntiles, kWgradBlocks);
-  const dim3 grid(nblk, 9, nitems), block(256);
+  const dim3 grid((unsigned)nblk * 9 * nitems), block(256);
   const int* L = lat.L;
   const long is = act_len(lat, cin), gs = act_len(lat, cout);
   const int V = (int)lat.V, nch = (int)lat.ntiles;
   if (cin == 4 && cout == 16)
-    hipLaunchKernelGGL((k_ptc_wgrad<4, 16>), grid, block, 0, s, U, in, g, L[0], L[1], L[2], L[3], V, nch, is, gs,
-                       part);
+    hipLaunchKernelGGL((k_ptc_wgrad<4, 16>), grid, block, 0, s, U, in, g, L[0], L[1], L[2], L[3], V, nch, nblk, is,
+                       gs, part);
   else if (cin == 16 && cout == 16)
-    hipLaunchKernelGGL((k_ptc_wgrad<16, 16>), grid, block, 0, s, U, in, g, L[0], L[1], L[2], L[3], V, nch, is, gs,
-                       part);
+    hipLaunchKernelGGL((k_ptc_wgrad<16, 16>), grid, block, 0, s, U, in, g, L[0], L[1], L[2], L[3], V, nch, nblk, is,
+                       gs, part);
   else
-    hipLaunchKernelGGL((k_ptc_wgrad<16, 4>), grid, block, 0, s, U, in, g, L[0], L[1], L[2], L[3], V, nch, is, gs,
-                       part);
+    hipLaunchKernelGGL((k_ptc_wgrad<16, 4>), grid, block, 0, s, U, in, g, L[0], L[1], L[2], L[3], V, nch, nblk, is,
+                       gs, part);
   const int ne = 9 * cout * cin;
-  hipLaunchKernelGGL(k_ptc_wgrad_reduce, dim3((ne + 255) / 256), dim3(256), 0, s, part, nitems, ne, nblk, G);
+  hipLaunchKernelGGL(k_ptc_wgrad_reduce, dim3((ne + 3) / 4), dim3(256), 0, s, part, nitems, ne, nblk, G);
   DL_HIP(hipGetLastError());
 }
 
@@ -569,7 +758,7 @@ void forward(dl_net* net, dl_op* op, int nitems, const double2* B, float2* Y, bo
                      (const double*)a.inv_s.get());
   DL_HIP(hipGetLastError());
   const float2* W = net->W.get();
-  launch_layer(s, lat, U, a.a0.get(), a.a1.get(), keep ? a.z1.get() : nullptr, W + net_weight_offset(0), 4, 16, true,
+  launch_layer(s, lat, U, a.a0.get(), a.a1.get(), keep ? a.z1.get() : nullptr, W + net_weight_offset(0), 4, 16, 1,
                nitems, nullptr);
   if (bf16 && !keep) {
     // inference: the 16 -> 16 layer's channel mixing in BF16 on the matrix cores
@@ -578,15 +767,15 @@ void forward(dl_net* net, dl_op* op, int nitems, const double2* B, float2* Y, bo
     hipLaunchKernelGGL(k_ptc_wfrag16, dim3((9 * 2 * 64 + 255) / 256), dim3(256), 0, s, W + net_weight_offset(1), fr);
     const int* L = lat.L;
     const int ntiles = (int)lat.ntiles;
-    hipLaunchKernelGGL((k_ptc_layer16_mfma<true>), dim3((ntiles + 3) / 4, nitems), dim3(256), 0, s, U, a.a1.get(),
-                       a.a2.get(), fr, L[0], L[1], L[2], L[3], (int)lat.V, ntiles, act_len(lat, 16),
-                       act_len(lat, 16), nullptr);
+    hipLaunchKernelGGL((k_ptc_layer16_mfma<true>), dim3((unsigned)ntiles * nitems), dim3(128), 0, s, U, a.a1.get(),
+                       a.a2.get(), fr, L[0], L[1], L[2], L[3], (int)lat.V, ntiles, act_len(lat, 16), act_len(lat, 16),
+                       nullptr);
     DL_HIP(hipGetLastError());
   } else {
     launch_layer(s, lat, U, a.a1.get(), a.a2.get(), keep ? a.z2.get() : nullptr, W + net_weight_offset(1), 16, 16,
-                 true, nitems, nullptr);
+                 1, nitems, nullptr);
   }
-  launch_layer(s, lat, U, a.a2.get(), Y, nullptr, W + net_weight_offset(2), 16, 4, false, nitems, a.s.get());
+  launch_layer(s, lat, U, a.a2.get(), Y, nullptr, W + net_weight_offset(2), 16, 4, 0, nitems, a.s.get());
 }
 
 }  // namespace
@@ -727,23 +916,17 @@ double net_loss_grad(dl_net* net, dl_op* op, int nitems, const double2* B, const
   float2* W = net->W.get();
   float2* G = net->G.get();
   float2* Wt = net->Wt.get();
-  const unsigned nl16 = (unsigned)((lat.V * 16 + 255) / 256);
   // layer 3 (16 -> 4)
   layer_wgrad(s, lat, U, a.a2.get(), a.g4.get(), 16, 4, nitems, a.part.get(), G + net_weight_offset(2));
   hipLaunchKernelGGL(k_ptc_adjoint_weights, dim3((9 * 64 + 255) / 256), dim3(256), 0, s, W + net_weight_offset(2),
                      Wt + net_weight_offset(2), 16, 4);
-  launch_layer(s, lat, U, a.g4.get(), a.g16a.get(), nullptr, Wt + net_weight_offset(2), 4, 16, false, nitems,
-               nullptr);
-  hipLaunchKernelGGL(k_ptc_nonlin_bwd, dim3(nl16, nitems), dim3(256), 0, s, a.z2.get(), a.g16a.get(), 16,
-                     (int)lat.V, act_len(lat, 16));
+  launch_layer(s, lat, U, a.g4.get(), a.g16a.get(), a.z2.get(), Wt + net_weight_offset(2), 4, 16, 2, nitems, nullptr);
   // layer 2 (16 -> 16)
   layer_wgrad(s, lat, U, a.a1.get(), a.g16a.get(), 16, 16, nitems, a.part.get(), G + net_weight_offset(1));
   hipLaunchKernelGGL(k_ptc_adjoint_weights, dim3((9 * 256 + 255) / 256), dim3(256), 0, s, W + net_weight_offset(1),
                      Wt + net_weight_offset(1), 16, 16);
-  launch_layer(s, lat, U, a.g16a.get(), a.g16b.get(), nullptr, Wt + net_weight_offset(1), 16, 16, false, nitems,
+  launch_layer(s, lat, U, a.g16a.get(), a.g16b.get(), a.z1.get(), Wt + net_weight_offset(1), 16, 16, 2, nitems,
                nullptr);
-  hipLaunchKernelGGL(k_ptc_nonlin_bwd, dim3(nl16, nitems), dim3(256), 0, s, a.z1.get(), a.g16b.get(), 16,
-                     (int)lat.V, act_len(lat, 16));
   // layer 1 (4 -> 16): weight gradient only
   layer_wgrad(s, lat, U, a.a0.get(), a.g16b.get(), 4, 16, nitems, a.part.get(), G + net_weight_offset(0));
   DL_HIP(hipGetLastError());

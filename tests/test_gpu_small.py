@@ -154,3 +154,41 @@ def test_solves_on_box_stencil(gpu_ctx, storage, kind, variant, monkeypatch):
     for b, x in zip(B, X):
         assert np.linalg.norm(b.ravel() - ora.M(x.ravel())) <= 1.0001e-10 * np.linalg.norm(b)
     op.close()
+
+
+# Network kernels at the edges of their split: fewer and more 64-site tiles than the weight gradient's 64
+# chunk groups, a last tile that is not full, one field and three.  FP32 sums of 9 * 16 * 3 products over
+# three layers against the FP64 oracle: 3 * 432 * 6e-8 = 8e-5, so 1e-4; the same for BF16 mixing against
+# the oracle that rounds the same operands.
+@pytest.mark.parametrize("dims,nf", [((3, 5, 2, 7), 1), ((6, 5, 13, 11), 3), ((8, 8, 8, 9), 1)])
+def test_network_tiles_and_chunks(gpu_ctx, dims, nf):
+    from lattice_inputs import su3_links
+    from oracle import lowp, ptc
+    from paper_0901_3163_amd import deflan
+    U = su3_links(dims, 950)
+    w = ptc.init_weights(951, scale=1.0)
+    ora = dirac.WilsonOperator(U, dims, 0.12)
+    M = lambda v: ora.M(v.ravel()).reshape(v.shape)
+    Mdag = lambda v: ora.Mdag(v.ravel()).reshape(v.shape)
+    B = np.stack([gaussian_spinor(dims, 952 + i) for i in range(nf)])
+    X = np.stack([0.4 * gaussian_spinor(dims, 960 + i) for i in range(nf)])
+    Ls, Gs = zip(*[ptc.loss_and_grad(U, w, B[i], X[i], dims, M, Mdag) for i in range(nf)])
+    op = deflan.Operator(gpu_ctx, dims, U, 0.12, deflan.DL_G5M)
+    net = deflan.Net(gpu_ctx, w)
+    L, G = net.loss_grad(op, B, X)
+    Y, Y16 = net.apply(op, B), net.apply(op, B, prec=deflan.DL_BF16)
+    net.close()
+    op.close()
+
+    def close(a, b):
+        return np.linalg.norm(np.ravel(a) - np.ravel(b)) <= 1e-4 * np.linalg.norm(np.ravel(b))
+
+    assert abs(L - np.mean(Ls)) <= 1e-4 * np.mean(Ls)
+    off = 0
+    for l in range(3):
+        n = 9 * ptc.WIDTHS[l + 1] * ptc.WIDTHS[l]
+        assert close(G[off:off + n], np.mean(Gs, axis=0)[off:off + n])
+        off += n
+    for i in range(nf):
+        assert close(Y[i], ptc.forward(U, w, B[i], dims))
+        assert close(Y16[i], ptc.forward_lowp(U, w, B[i], dims, lowp.round_bf16))
