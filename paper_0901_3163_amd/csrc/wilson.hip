@@ -1613,10 +1613,13 @@ __device__ __forceinline__ void eo_coords(int h, int par, int Lx, int Ly, int Lz
   x = 2 * xh + ((par + y + z + t) & 1);
 }
 
-// acc = D_{par, 1-par} applied at half site h (input: half field of the other parity, in storage SV)
-template <int SF, class C, class SV>
-__device__ __forceinline__ void eo_hops(const C* __restrict__ U, const SV* __restrict__ in, int h, int par, int Lx,
-                                        int Ly, int Lz, int Lt, C acc[12]) {
+// acc = D_{par, 1-par} applied at half site h (input: half fields of the other parity, in storage SV)
+// for RT right-hand sides.  As in k_wilson_box every hop is unrolled with its own projection, and the next hop's
+// link and spinors are requested before this one's arithmetic (FP64: the link only).
+template <int SF, int RT, class C, class SV>
+__device__ __forceinline__ void eo_hops(const C* __restrict__ U, const SV* __restrict__ in, long fstride,
+                                        const bool on[RT], int h, int par, int Lx, int Ly, int Lz, int Lt,
+                                        C acc[RT][12]) {
   int x, y, z, t;
   eo_coords(h, par, Lx, Ly, Lz, x, y, z, t);
   const int sy = Lx, sz = Lx * Ly, st = Lx * Ly * Lz;
@@ -1625,82 +1628,178 @@ __device__ __forceinline__ void eo_hops(const C* __restrict__ U, const SV* __res
   const int fy = y == Ly - 1 ? (1 - Ly) * sy : sy, by = y == 0 ? (Ly - 1) * sy : -sy;
   const int fz = z == Lz - 1 ? (1 - Lz) * sz : sz, bz = z == 0 ? (Lz - 1) * sz : -sz;
   const int ft = t == Lt - 1 ? (1 - Lt) * st : st, bt = t == 0 ? (Lt - 1) * st : -st;
+  constexpr bool PF = sizeof(C) == 8;
+  auto link = [&](int s, int mu) {
+    Lk<C> l;
+    const C* up = U + lk_base(s, mu);
 #pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = czero<C>();
-#pragma unroll 1
-  for (int mu = 0; mu < 4; ++mu) {
-    const int df = mu == 0 ? fx : mu == 1 ? fy : mu == 2 ? fz : ft;
-    const int db = mu == 0 ? bx : mu == 1 ? by : mu == 2 ? bz : bt;
-    hop<SF, false>(U, in, mu, (site + df) >> 1, site, acc);
-    hop<-SF, true>(U, in, mu, (site + db) >> 1, site + db, acc);
+    for (int e = 0; e < 9; ++e) l.e[e] = up[e * kTile];
+    return l;
+  };
+  auto spinor = [&](int j, int nb) {
+    SpRaw<SV> r;
+    const SV* pp = in + j * fstride + sp_base(nb >> 1);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) r.e[c] = pp[c * kTile];
+    return r;
+  };
+  Lk<C> u = link(site, 0);
+  SpRaw<SV> raw[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    if (PF && on[j]) raw[j] = spinor(j, site + fx);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[j][c] = czero<C>();
   }
+  auto hop = [&](auto MUc, auto Sc, auto DAGc, int nb, auto LASTc, int next_site, int next_mu, int next_nb) {
+    constexpr int MU = decltype(MUc)::value, S = decltype(Sc)::value;
+    constexpr bool DAG = decltype(DAGc)::value, LAST = decltype(LASTc)::value;
+    // opaque here, so that the loads of later hops are not gathered ahead of this one's arithmetic
+    asm volatile("" : "+v"(next_site), "+v"(next_nb), "+v"(nb));
+    Lk<C> un{};
+    if (!LAST) un = link(next_site, next_mu);
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+      if (!on[j]) continue;
+      C p[12], hs[6], g[6];
+      if (!PF) raw[j] = spinor(j, nb);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) p[c] = sldv(raw[j].e[c]);
+      if (PF && !LAST) raw[j] = spinor(j, next_nb);
+      project<MU, S>(p, hs);
+      mul_half<DAG>(u.e, hs, g);
+      reconstruct<MU, S>(acc[j], g);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[j][c].x), "+v"(acc[j][c].y));
+    }
+    u = un;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr std::integral_constant<int, SF> P{};
+  constexpr std::integral_constant<int, -SF> N{};
+  constexpr std::integral_constant<int, 0> X{};
+  constexpr std::integral_constant<int, 1> Y{};
+  constexpr std::integral_constant<int, 2> Z{};
+  constexpr std::integral_constant<int, 3> T{};
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  hop(X, P, no, site + fx, no, site + bx, 0, site + bx);
+  hop(X, N, yes, site + bx, no, site, 1, site + fy);
+  hop(Y, P, no, site + fy, no, site + by, 1, site + by);
+  hop(Y, N, yes, site + by, no, site, 2, site + fz);
+  hop(Z, P, no, site + fz, no, site + bz, 2, site + bz);
+  hop(Z, N, yes, site + bz, no, site, 3, site + ft);
+  hop(T, P, no, site + ft, no, site + bt, 3, site + bt);
+  hop(T, N, yes, site + bt, yes, site, 3, site);
 }
 
+// Which rhs of a group of RT the block works on; false if none.
+template <int RT>
+__device__ __forceinline__ bool eo_group(int rg, int nrhs, const int* __restrict__ active, bool on[RT]) {
+  bool any = false;
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const int r = rg * RT + j;
+    on[j] = r < nrhs && (!active || active[r]);
+    any |= on[j];
+  }
+  return any;
+}
+
+// Both stages: bound by the latency of their loads (the links of one parity are every other site, so half
+// of each line is not used; 12 FP32 rhs of 16^3 x 32 move 1.05 GB from the caches a stage and take 21 us of
+// instruction issue).  Two rhs a thread share the link loads, each hop's loads are issued a hop ahead and
+// a site block's rhs are neighbours on one XCD: stage 1 126 -> 78 us, stage 2 139 -> 83 us.
 // Stage 1: tmp (arithmetic precision) = D_{1-par0, par0} in for the rhs of the launch.
-template <class R, class SV, int WHICH>
-__global__ void __launch_bounds__(256)
+template <class R, class SV, int WHICH, int RT>
+__global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2)
 k_eo_hop1(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ in, typename CT<R>::type* __restrict__ tmp,
-          long fstride, int nrhs, int Lx, int Ly, int Lz, int Lt, long V, long Vpad, int par,
+          long fstride, int nrhs, int ngroups, int Lx, int Ly, int Lz, int Lt, long V, long Vpad, int par,
           const int* __restrict__ active) {
   using C = typename CT<R>::type;
-  const int rhs = (int)blockIdx.x % nrhs, sb = (int)blockIdx.x / nrhs;
-  if (active && !active[rhs]) return;
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int rg = lb % ngroups, sb = lb / ngroups;
+  bool on[RT];
+  if (!eo_group<RT>(rg, nrhs, active, on)) return;
   const int h = sb * 256 + (int)threadIdx.x;
-  C* op = tmp + rhs * fstride;
-  if (h >= V && h < Vpad) {
+  C* op = tmp + rg * RT * fstride;
+  if (h >= Vpad) return;
+  C acc[RT][12];
+  if (h >= V) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) op[sp_base(h) + c * kTile] = czero<C>();
+    for (int j = 0; j < RT; ++j)
+#pragma unroll
+      for (int c = 0; c < 12; ++c) acc[j][c] = czero<C>();
+  } else {
+    constexpr int SF = (WHICH == 1) ? 1 : -1;
+    eo_hops<SF, RT>(U, in + rg * RT * fstride, fstride, on, h, par, Lx, Ly, Lz, Lt, acc);
   }
-  if (h >= V) return;
-  constexpr int SF = (WHICH == 1) ? 1 : -1;
-  C acc[12];
-  eo_hops<SF>(U, in + rhs * fstride, h, par, Lx, Ly, Lz, Lt, acc);
 #pragma unroll
-  for (int c = 0; c < 12; ++c) op[sp_base(h) + c * kTile] = acc[c];
+  for (int j = 0; j < RT; ++j) {
+    if (!on[j]) continue;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) op[j * fstride + sp_base(h) + c * kTile] = acc[j][c];
+  }
 }
 
 // Stage 2: out = scale * (in - kappa^2 D_{par, 1-par} tmp) (gamma5 on the result for WHICH 2), with
 // the fused reduction of the result (RED 1: ||out||^2, RED 2: Re<in, out>) per block.
-template <class R, class SV, int WHICH, int RED>
-__global__ void __launch_bounds__(256)
+template <class R, class SV, int WHICH, int RED, int RT>
+__global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2)
 k_eo_schur(const typename CT<R>::type* __restrict__ U, const typename CT<R>::type* __restrict__ tmp,
-           const SV* __restrict__ in, SV* __restrict__ out, long fstride, int nrhs, double kappa2, int Lx, int Ly,
-           int Lz, int Lt, long V, long Vpad, int par, int nbs, const double* __restrict__ scale,
+           const SV* __restrict__ in, SV* __restrict__ out, long fstride, int nrhs, int ngroups, double kappa2, int Lx,
+           int Ly, int Lz, int Lt, long V, long Vpad, int par, int nbs, const double* __restrict__ scale,
            const int* __restrict__ active, double* __restrict__ part) {
   using C = typename CT<R>::type;
-  const int rhs = (int)blockIdx.x % nrhs, sb = (int)blockIdx.x / nrhs;
-  if (active && !active[rhs]) return;
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int rg = lb % ngroups, sb = lb / ngroups;
+  bool on[RT];
+  if (!eo_group<RT>(rg, nrhs, active, on)) return;
   const int h = sb * 256 + (int)threadIdx.x;
-  SV* op = out + rhs * fstride;
-  double red = 0.0;
+  double red[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) red[j] = 0.0;
+  SV* op = out + rg * RT * fstride;
   if (h >= V && h < Vpad) {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) sst(op + sp_base(h) + c * kTile, CT<R>::make(0, 0));
+    for (int j = 0; j < RT; ++j)
+      if (on[j]) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) sst(op + j * fstride + sp_base(h) + c * kTile, CT<R>::make(0, 0));
+      }
   }
   if (h < V) {
     constexpr int SF = (WHICH == 1) ? 1 : -1;
-    C acc[12];
-    eo_hops<SF>(U, tmp + rhs * fstride, h, par, Lx, Ly, Lz, Lt, acc);
-    const R sc = scale ? (R)scale[rhs] : (R)1;
+    C acc[RT][12];
+    eo_hops<SF, RT>(U, tmp + rg * RT * fstride, fstride, on, h, par, Lx, Ly, Lz, Lt, acc);
     const R mk = (R)(-kappa2);
-    const SV* ip = in + rhs * fstride + sp_base(h);
-    R sred = 0;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      const C p = sld(ip + c * kTile);
-      C r = CT<R>::make(fma(mk, acc[c].x, p.x) * sc, fma(mk, acc[c].y, p.y) * sc);
-      if (WHICH == 2 && c >= 6) r = CT<R>::make(-r.x, -r.y);
-      sst(op + sp_base(h) + c * kTile, r);
-      if (RED == 1) sred = fma(r.x, r.x, fma(r.y, r.y, sred));
-      if (RED == 2) sred = fma(p.x, r.x, fma(p.y, r.y, sred));
+    for (int j = 0; j < RT; ++j) {
+      if (!on[j]) continue;
+      const R sc = scale ? (R)scale[rg * RT + j] : (R)1;
+      const SV* ip = in + (rg * RT + j) * fstride + sp_base(h);
+      R sred = 0;
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        const C p = sld(ip + c * kTile);
+        C r = CT<R>::make(fma(mk, acc[j][c].x, p.x) * sc, fma(mk, acc[j][c].y, p.y) * sc);
+        if (WHICH == 2 && c >= 6) r = CT<R>::make(-r.x, -r.y);
+        sst(op + j * fstride + sp_base(h) + c * kTile, r);
+        if (RED == 1) sred = fma(r.x, r.x, fma(r.y, r.y, sred));
+        if (RED == 2) sred = fma(p.x, r.x, fma(p.y, r.y, sred));
+      }
+      if (RED == 1) red[j] = (double)sred;
+      if (RED == 2) red[j] = (double)sred * sc;
     }
-    if (RED == 1) red = (double)sred;
-    if (RED == 2) red = (double)sred * sc;
   }
   if (RED != 0) {
     __shared__ double lds[256 / 64];
-    const double s = block_sum<256>(red, lds);
-    if (threadIdx.x == 0) part[(long)rhs * nbs + sb] = s;
+#pragma unroll
+    for (int j = 0; j < RT; ++j) {
+      if (!on[j]) continue;  // uniform over the block
+      const double s = block_sum<256>(red[j], lds);
+      if (threadIdx.x == 0) part[(long)(rg * RT + j) * nbs + sb] = s;
+    }
   }
 }
 
@@ -1726,6 +1825,28 @@ static void* eo_buffer(hipStream_t s, size_t bytes) {
   return g_eo_scratch[s].get();
 }
 
+template <class R, class SV, int RT>
+static void launch_eo(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, int which, const SV* in,
+                      cplx_t<R>* tmp, SV* out, long fstride, int nrhs, int red, const double* scale, const int* active,
+                      double* part, int nbs) {
+  const int* L = lat.L;
+  const long Vpad = lat.ntiles * kTile;
+  const int ngroups = (nrhs + RT - 1) / RT;
+  const dim3 grid((unsigned)((long)nbs * ngroups)), block(256);
+  // stage 1: odd intermediate D_oe in (par 1 output); stage 2: even result
+#define DL_EO1(WH) hipLaunchKernelGGL((k_eo_hop1<R, SV, WH, RT>), grid, block, 0, s, U, in, tmp, fstride, nrhs, \
+                                      ngroups, L[0], L[1], L[2], L[3], lat.V, Vpad, 1, active)
+#define DL_EO2(WH, RD) hipLaunchKernelGGL((k_eo_schur<R, SV, WH, RD, RT>), grid, block, 0, s, U, tmp, in, out, \
+                                          fstride, nrhs, ngroups, kappa * kappa, L[0], L[1], L[2], L[3], lat.V, Vpad, \
+                                          0, nbs, scale, active, part)
+  if (which == 1) DL_EO1(1); else DL_EO1(0);
+  if (which == 0) { if (red == 0) DL_EO2(0, 0); else if (red == 1) DL_EO2(0, 1); else DL_EO2(0, 2); }
+  else if (which == 1) { if (red == 0) DL_EO2(1, 0); else if (red == 1) DL_EO2(1, 1); else DL_EO2(1, 2); }
+  else { if (red == 0) DL_EO2(2, 0); else if (red == 1) DL_EO2(2, 1); else DL_EO2(2, 2); }
+#undef DL_EO1
+#undef DL_EO2
+}
+
 template <class R, class SV>
 static int wilson_eo(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, int which, const SV* in,
                      SV* out, long fstride, int nrhs, int red, const double* scale, const int* active, double* part) {
@@ -1733,21 +1854,15 @@ static int wilson_eo(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, doub
   const int nbs = (int)((lat.V + 255) / 256);
   if (red && nbs > kMaxPartials) fail(DL_E_INVALID, "lattice too large for fused reduction");
   C* tmp = static_cast<C*>(eo_buffer(s, (size_t)nrhs * fstride * sizeof(C)));
-  const int* L = lat.L;
-  const long Vpad = lat.ntiles * kTile;
-  const dim3 grid((unsigned)((long)nbs * nrhs)), block(256);
-  // stage 1: odd intermediate D_oe in (par 1 output); stage 2: even result
-#define DL_EO1(WH) hipLaunchKernelGGL((k_eo_hop1<R, SV, WH>), grid, block, 0, s, U, in, tmp, fstride, nrhs, L[0], L[1], \
-                                      L[2], L[3], lat.V, Vpad, 1, active)
-#define DL_EO2(WH, RD) hipLaunchKernelGGL((k_eo_schur<R, SV, WH, RD>), grid, block, 0, s, U, tmp, in, out, fstride, \
-                                          nrhs, kappa * kappa, L[0], L[1], L[2], L[3], lat.V, Vpad, 0, nbs, scale, \
-                                          active, part)
-  if (which == 1) DL_EO1(1); else DL_EO1(0);
-  if (which == 0) { if (red == 0) DL_EO2(0, 0); else if (red == 1) DL_EO2(0, 1); else DL_EO2(0, 2); }
-  else if (which == 1) { if (red == 0) DL_EO2(1, 0); else if (red == 1) DL_EO2(1, 1); else DL_EO2(1, 2); }
-  else { if (red == 0) DL_EO2(2, 0); else if (red == 1) DL_EO2(2, 1); else DL_EO2(2, 2); }
-#undef DL_EO1
-#undef DL_EO2
+  // two rhs a thread share the links; only where that still leaves two blocks for each of the 256 CUs
+  if constexpr (sizeof(R) == 4) {
+    if (nrhs > 1 && (long)nbs * ((nrhs + 1) / 2) >= 512) {
+      launch_eo<R, SV, 2>(s, lat, U, kappa, which, in, tmp, out, fstride, nrhs, red, scale, active, part, nbs);
+      DL_HIP(hipGetLastError());
+      return red ? nbs : 0;
+    }
+  }
+  launch_eo<R, SV, 1>(s, lat, U, kappa, which, in, tmp, out, fstride, nrhs, red, scale, active, part, nbs);
   DL_HIP(hipGetLastError());
   return red ? nbs : 0;
 }
@@ -1786,8 +1901,10 @@ k_eo_hop_f64(const double2* __restrict__ U, const double2* __restrict__ in, cons
     for (int c = 0; c < 12; ++c) out[sp_base(h) + c * kTile] = make_double2(0.0, 0.0);
   }
   if (h >= V) return;
-  double2 acc[12];
-  eo_hops<-1>(U, in, h, par, Lx, Ly, Lz, Lt, acc);
+  double2 accs[1][12];
+  const bool on[1] = {true};
+  eo_hops<-1, 1>(U, in, 0, on, h, par, Lx, Ly, Lz, Lt, accs);
+  double2* acc = accs[0];
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
     const double2 a = add ? add[sp_base(h) + c * kTile] : make_double2(0.0, 0.0);

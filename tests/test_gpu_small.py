@@ -192,3 +192,21 @@ def test_network_tiles_and_chunks(gpu_ctx, dims, nf):
     for i in range(nf):
         assert close(Y[i], ptc.forward(U, w, B[i], dims))
         assert close(Y16[i], ptc.forward_lowp(U, w, B[i], dims, lowp.round_bf16))
+
+
+# The even-odd apply with two right-hand sides a thread (from 512 blocks on) against one a thread: the same
+# operations in the same order, so the same bits; an odd number of right-hand sides leaves a half-empty pair.
+@pytest.mark.parametrize("which", ["M", "Mdag", "g5M"])
+def test_even_odd_two_rhs_a_thread_bits(gpu_ctx, which):
+    from lattice_inputs import su3_links
+    from paper_0901_3163_amd import deflan
+    dims = (16, 16, 16, 16)
+    op = deflan.Operator(gpu_ctx, dims, su3_links(dims, 970), 0.12, deflan.DL_G5M | deflan.DL_EVEN_ODD)
+    w = {"M": deflan.DL_APPLY_M, "Mdag": deflan.DL_APPLY_MDAG, "g5M": deflan.DL_APPLY_G5M}[which]
+    rng = np.random.default_rng(971)
+    P = rng.standard_normal((9, np.prod(dims) // 2, 4, 3)) + 1j * rng.standard_normal((9, np.prod(dims) // 2, 4, 3))
+    for prec in (deflan.DL_FP32, deflan.DL_BF16):
+        got = op.apply_batched(w, prec, P)
+        for i in range(len(P)):
+            assert np.array_equal(got[i], op.apply_batched(w, prec, P[i:i + 1])[0])
+    op.close()
