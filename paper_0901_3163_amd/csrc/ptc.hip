@@ -815,9 +815,14 @@ void NetActs::ensure(const Lattice& lat, int nitems) {
   gsc.alloc(nitems);
 }
 
-void net_apply(dl_net* net, dl_op* op, int nitems, const double2* B, double2* Y64, bool bf16) {
+const float2* net_guess(dl_net* net, dl_op* op, int nitems, const double2* B, bool bf16) {
   net->acts.ensure(op->lat, nitems);
   forward(net, op, nitems, B, net->acts.y.get(), false, bf16);
+  return net->acts.y.get();
+}
+
+void net_apply(dl_net* net, dl_op* op, int nitems, const double2* B, double2* Y64, bool bf16) {
+  net_guess(net, op, nitems, B, bf16);
   hipLaunchKernelGGL(k_to_f64, dim3(kStreamBlocks, nitems), dim3(256), 0, net->ctx->stream, net->acts.y.get(), Y64,
                      op->lat.nc);
   DL_HIP(hipGetLastError());

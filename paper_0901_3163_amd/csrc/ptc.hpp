@@ -41,6 +41,9 @@ namespace dl {
 // Y64 (tiled FP64, nitems fields at stride lat.nc) = net(B) for tiled FP64 B; bf16: the 16 -> 16
 // layer's channel mixing with BF16 operands on the matrix cores (FP32 accumulation).
 void net_apply(dl_net* net, dl_op* op, int nitems, const double2* B, double2* Y64, bool bf16 = false);
+// The same left in FP32 in the network's own buffer, for a caller that widens as it converts the layout
+// (16 fields of 16^3 x 32: a pass of 92 us less, and half the bytes read by the conversion).
+const float2* net_guess(dl_net* net, dl_op* op, int nitems, const double2* B, bool bf16 = false);
 // Mean over items of ||M (net(b) - x)||^2 / ||b||^2; with grad, net->G holds its real gradient.
 // With net->proj set (eigenvectors Y of op's M^dag M, H = Y^H M^dag M Y), the error d = net(b) - x
 // is first replaced by what the D-CG start leaves of it, d' = d - Y H^-1 Y^H M^dag M d.
