@@ -26,6 +26,7 @@
 // and beta_j are real, and the restart matrices are real combinations.
 #include "internal.hpp"
 #include "cplx.hpp"
+#include "rank.hpp"
 #include "small.hpp"
 
 namespace dl {
@@ -390,17 +391,9 @@ static void jacobi(hipStream_t s, int n, const double* A, int ld, int from, doub
   DL_HIP(hipGetLastError());
 }
 
-// perm[rank] = i with ranks by (key ascending, index ascending).
+// perm[rank] = i with ranks by (key ascending, NaN last, index ascending): every entry is set.
 __device__ void rank_sort(int n, const double* key, int* perm) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double ki = key[i];
-    int r = 0;
-    for (int j = 0; j < n; ++j) {
-      const double kj = key[j];
-      r += (kj < ki) || (kj == ki && j < i);
-    }
-    perm[r] = i;
-  }
+  for (int i = threadIdx.x; i < n; i += blockDim.x) perm[key_rank(n, key, i)] = i;
   __syncthreads();
 }
 
@@ -415,7 +408,7 @@ __global__ void __launch_bounds__(256) k_eigh_sort(int n, const double* __restri
   __syncthreads();
   const double kj = key[j];
   int r = 0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) r += (key[i] < kj) || (key[i] == kj && i < j);
+  for (int i = threadIdx.x; i < n; i += blockDim.x) r += key_before(key[i], i, kj, j);
   if (r) atomicAdd(&rank, r);
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += blockDim.x) Z[(long)i * n + rank] = Zt[(long)i * n + j];
@@ -689,7 +682,7 @@ k_mr_trsm(int m, const double* __restrict__ In, const double* __restrict__ Rr, d
     if (lane + 64 * k < m) Out[(long)(lane + 64 * k) * m + row] = a[k];
 }
 
-// Kept harmonic Ritz vector l = blockIdx.x (the l-th smallest |1/mu|; ties: 1/mu ascending, then
+// Kept harmonic Ritz vector l = blockIdx.x (the l-th smallest |1/mu|, NaN last; ties: 1/mu ascending, then
 // index): g_l = R^-1 y_l into row l of Q (m + 1 entries, the last zero); hth[l] = 1/mu.
 template <int NR>
 __global__ void __launch_bounds__(64)
@@ -700,15 +693,8 @@ k_mr_ritz(int m, const double* __restrict__ mu, const double* __restrict__ Z, co
   const int lane = threadIdx.x, l = blockIdx.x;
   for (int i = lane; i < m; i += 64) key[i] = mu[i] != 0.0 ? 1.0 / mu[i] : INFINITY;
   __syncthreads();
-  for (int i = lane; i < m; i += 64) {
-    const double ki = key[i], ai = fabs(ki);
-    int r = 0;
-    for (int j = 0; j < m; ++j) {
-      const double kj = key[j], aj = fabs(kj);
-      r += (aj < ai) || (aj == ai && (kj < ki || (kj == ki && j < i)));
-    }
-    if (r == l) scol = i;
-  }
+  for (int i = lane; i < m; i += 64)
+    if (key_rank_abs(m, key, i) == l) scol = i;
   __syncthreads();
   const int col = scol;
   double a[NR];
