@@ -14,7 +14,7 @@ namespace dl {
 // ---- layout ----------------------------------------------------------------
 // Caller's layout ([site][12] double2) <-> tiled fields in FP64, FP32 or BF16 storage (rounded through
 // FP32).  One wave per 64-site tile: 12 coalesced accesses on each side, transposed in LDS (rows of
-// 13 elements; a wave's LDS accesses are in order, so no barrier), with the padding sites of the
+// 13 elements; each wave its own, so no block barrier), with the padding sites of the
 // last tile written as zeros.  Bound by the copy's bytes.  Rounding here rather than in a pass of its
 // own, and no zeroing pass before: for 12 fields of 16^3 x 32 to BF16 38 + 142 + 85 us became one
 // 61 us launch (378 MB, 6.2 TB/s), and 64 + 111 us back became 54.  The caller's side is accessed
@@ -69,7 +69,7 @@ k_pack_spinor(const double2* __restrict__ in, SV* __restrict__ out, long V, long
     const int e = k * 64 + lane;
     st[e / kSpin * kPackRow + e % kSpin] = pack_cast<SV>(v[k]);
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_exchange();
   SV* dst = out + f * nc + e0 + lane;
 #pragma unroll
   for (int c = 0; c < kSpin; ++c) dst[c * kTile] = st[lane * kPackRow + c];
@@ -91,7 +91,7 @@ k_unpack_spinor(const SV* __restrict__ in, double2* __restrict__ out, long V, lo
   for (int c = 0; c < kSpin; ++c) v[c] = src[c * kTile];
 #pragma unroll
   for (int c = 0; c < kSpin; ++c) st[lane * kPackRow + c] = v[c];
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_exchange();
   double2* dst = out + f * V * kSpin + e0;
 #pragma unroll
   for (int k = 0; k < kSpin; ++k) {

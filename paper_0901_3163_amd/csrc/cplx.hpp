@@ -202,6 +202,15 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Between a lane's LDS stores and other lanes' loads of them within one wave.  The hardware keeps a
+// wave's LDS accesses in order; the fences keep the compiler's (the barrier alone orders no memory).
+// No instruction at wavefront scope.
+__device__ __forceinline__ void wave_lds_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum over a block of kBlock threads; result valid in thread 0.  Fixed order.
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* lds /* NT/64 */) {

@@ -293,7 +293,7 @@ k_jacobi_lds(int n, int rows, const double* __restrict__ A, int ld, int from, do
 }
 
 // Rows of Z = I J_1 J_2 ...: one wave per row, the row in LDS, lane t rotating pairs t, t + 64.
-// A wave's LDS accesses are in order, so rounds need no barrier; the log is read eight rounds ahead.
+// Only its own wave reads a row, so rounds need no block barrier; the log is read eight rounds ahead.
 __global__ void __launch_bounds__(256)
 k_jacobi_vec(int n, const double2* __restrict__ log, const int* __restrict__ rlist, const int* __restrict__ meta,
              double* __restrict__ Z) {
@@ -305,7 +305,7 @@ k_jacobi_vec(int n, const double2* __restrict__ log, const int* __restrict__ rli
   double* z = dyn + (long)wid * (n + 2);
   const int half = jac_half(n), np = n + (n & 1);
   for (int j = lane; j <= n; j += 64) z[j] = j == row ? 1.0 : 0.0;
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_exchange();
   const int nr = meta[0];
   for (int k0 = 0; k0 < nr; k0 += kAhead) {
     double2 c[kAhead][kPer];
@@ -334,7 +334,7 @@ k_jacobi_vec(int n, const double2* __restrict__ log, const int* __restrict__ rli
           z[q] = c[u][h].y * zp + c[u][h].x * zq;
         }
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_exchange();
     }
   }
   for (int j = lane; j < n; j += 64) Z[(long)row * n + j] = z[j];
@@ -597,14 +597,14 @@ k_mr_qr(int m, const double* __restrict__ Tb, const double* __restrict__ c, doub
     __syncthreads();
   }
   if (wid == 0) {
-    // d = R^-1 e, column-oriented (one wave: its LDS accesses are in order)
+    // d = R^-1 e, column-oriented, in one wave
     for (int i = lane; i <= m; i += 64) ev[i] = C[(long)m * lp + i];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_exchange();
     for (int j = m - 1; j >= 0; --j) {
       const double dj = ev[j] / al[j];
       if (lane == 0) dv[j] = dj;
       for (int i = lane; i < j; i += 64) ev[i] -= C[(long)j * lp + i] * dj;
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_exchange();
     }
   } else if (wid == 1) {
     // q = H_0 ... H_{m-1} e_m
