@@ -25,7 +25,7 @@
 namespace dl {
 
 // BF16 complex storage: the upper halves of the two FP32 parts (round to nearest even).
-struct __align__(4) bf2 {
+struct alignas(4) bf2 {
   unsigned short x, y;
 };
 
@@ -169,6 +169,8 @@ struct WilsonCfg {
   int variant = 0;
   int order = 0;
 };
+// The variant whose kernel `variant` launches on this lattice in this precision.
+int wilson_shape(const Lattice& lat, int variant, bool fp64);
 // which: 0 M, 1 M^dag, 2 gamma5 M.  red: 0 none, 1 ||out||^2 partials, 2 Re<in,out> partials.
 // Returns the number of partials per rhs written to `part` (0 if red == 0).
 int wilson_f64(hipStream_t s, const Lattice& lat, const double2* U, double kappa, int which,
@@ -188,6 +190,8 @@ void eo_hop_f64(hipStream_t s, const Lattice& lat, const double2* U, double kapp
 // Batched Wilson apply in FP64 (R = double) or FP32 (R = float): nrhs fields at stride fstride.
 // Partials (red != 0) are column-major [nrhs][wilson_nbs(lat)].  Returns wilson_nbs(lat) or 0.
 int wilson_nbs(const Lattice& lat, const WilsonCfg& cfg);
+// Blocks of a launch (an upper bound where several rhs share an LDS stage).
+long wilson_grid(const Lattice& lat, const WilsonCfg& cfg, bool fp64, int nrhs);
 int wilson_max_nbs(const Lattice& lat);  // partials per rhs of the widest-grid variant
 // SV: spinor storage (double2 with R = double; float2 or bf2 with R = float); arithmetic in R.
 template <class R, class SV>

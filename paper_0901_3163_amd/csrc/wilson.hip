@@ -1357,8 +1357,8 @@ k_wilson_box(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
 // 15-17: k_wilson_mr with (threads per block, rhs per thread) = (256, 2), (256, 4), (128, 2).
 // 18-19: k_wilson_tmp with box blocks of whole x rows (T = 8, 16); where no box tiles the
 // slice they launch variants 12 and 13.  20: k_wilson_split, 64 sites per block.
-// 21-26: k_wilson_box with (rhs per block, T) = (1, 4), (1, 8), (1, 16), (2, 4), (2, 8), (2, 16) (FP64: one rhs
-// per block); where no box fits a slice they launch variants 4 to 6.
+// 21-26: k_wilson_box with (rhs per block, T) = (1, 4), (1, 8), (1, 16), (2, 4), (2, 8), (2, 16) (FP64: 24-26
+// are 21-23); where no box fits a slice they launch variants 4 to 6.
 static constexpr int kVariantNT[kWilsonVariants] = {256, 128, 512, 256, 256, 256, 256, 64, 64, 64, 64, 256, 256, 256, 256,
                                                     256, 256, 128, 256, 256, 64, 256, 256, 256, 256, 256, 256};
 static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16, 0,
@@ -1446,14 +1446,14 @@ static bool site_box(const Lattice& lat, int* by, int* bz) {
   return best < 1e300;
 }
 
-// The launch shape that variant v runs on this lattice: k_wilson_box needs a box, 32-bit byte offsets (the
-// FP64 links under 4 GB) and no more blocks a field than the fused reductions take.
-static int effective_variant(const Lattice& lat, int v) {
+// k_wilson_box needs a box, 32-bit byte offsets (the FP64 links under 4 GB) and no more blocks a field than the
+// fused reductions take; FP64 has registers for one rhs a block only.
+int wilson_shape(const Lattice& lat, int v, bool fp64) {
   int by, bz;
   if (v < kFirstBox) return v;
   if ((double)lat.ntiles * kTile * kLinkC * sizeof(double2) < 4294967296.0 && site_box(lat, &by, &bz) &&
       (long)(lat.L[1] / by) * (lat.L[2] / bz) * ((lat.L[3] + kVariantT[v] - 1) / kVariantT[v]) <= kMaxPartials)
-    return v;
+    return fp64 ? kFirstBox + (v - kFirstBox) % 3 : v;
   return 4 + (v - kFirstBox) % 3;
 }
 
@@ -1575,11 +1575,9 @@ static void launch_variant(int variant, hipStream_t s, const Lattice& lat, const
       launch_mr<R, SV, WHICH, RED, 128, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs);
       break;
     case 24: case 25: case 26:
-      if constexpr (sizeof(R) == 4) {
+      if constexpr (sizeof(R) == 4)
         launch_box<R, SV, WHICH, RED, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
-        break;
-      }
-      [[fallthrough]];
+      break;
     case 21: case 22: case 23:
       launch_box<R, SV, WHICH, RED, 1>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
       break;
@@ -1945,7 +1943,7 @@ int wilson_residual_f64(hipStream_t s, const Lattice& lat, const double2* U, dou
   if ((lo == nullptr) == (r == nullptr)) fail(DL_E_INVALID, "the fused residual goes to r or to lo");
   // k_wilson_box with one rhs a block and chunks of 16 slices, in hardware block order (16^3 x 32, 64 rhs:
   // 1283 us by k_wilson_tm, 1122 here; chunks of 4 and 8 within 1% of it); k_wilson_tm where it has no box
-  const int v = effective_variant(lat, kFirstBox + 2);
+  const int v = wilson_shape(lat, kFirstBox + 2, true);
   const int nbs = tm_nb3(lat, v) * tm_chunks(lat, v);
   if (nbs > kMaxPartials) fail(DL_E_INVALID, "lattice too large for fused reduction");
   if ((long)nbs * nrhs > 2147483647L) fail(DL_E_INVALID, "grid too large");
@@ -1973,10 +1971,15 @@ int wilson_residual_f64(hipStream_t s, const Lattice& lat, const double2* U, dou
 
 int wilson_nbs(const Lattice& lat, const WilsonCfg& cfg) {
   if (lat.eo) return (int)((lat.V + 255) / 256);
-  const int v = effective_variant(lat, cfg.variant % kWilsonVariants);
+  const int v = wilson_shape(lat, cfg.variant % kWilsonVariants, false);  // (FP64 runs the same blocks of sites)
   if (kVariantT[v] > 0) return tm_nb3(lat, v) * tm_chunks(lat, v);
   const int nt = kVariantNT[v];
   return (int)((lat.V + nt - 1) / nt);
+}
+
+long wilson_grid(const Lattice& lat, const WilsonCfg& cfg, bool fp64, int nrhs) {
+  const int rt = kVariantRT[wilson_shape(lat, cfg.variant % kWilsonVariants, fp64)];
+  return (long)wilson_nbs(lat, cfg) * ((nrhs + rt - 1) / rt);
 }
 
 int wilson_max_nbs(const Lattice& lat) {
@@ -1990,10 +1993,10 @@ int wilson_batched(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double
                    const SV* in, SV* out, long fstride, int nrhs, int red, const double* scale,
                    const int* active, double* part, WilsonCfg cfg) {
   if (lat.eo) return wilson_eo<R, SV>(s, lat, U, kappa, which, in, out, fstride, nrhs, red, scale, active, part);
-  const int v = effective_variant(lat, cfg.variant % kWilsonVariants);
+  const int v = wilson_shape(lat, cfg.variant % kWilsonVariants, sizeof(R) == 8);
   const int nbs = wilson_nbs(lat, cfg);
   if (red && nbs > kMaxPartials) fail(DL_E_INVALID, "lattice too large for fused reduction");
-  if ((long)nbs * nrhs > 2147483647L && (long)nbs * ((nrhs + kVariantRT[v] - 1) / kVariantRT[v]) > 2147483647L) fail(DL_E_INVALID, "grid too large");
+  if (wilson_grid(lat, cfg, sizeof(R) == 8, nrhs) > 2147483647L) fail(DL_E_INVALID, "grid too large");
   const int o = cfg.order;
 #define DL_W(WH, RD) launch_variant<R, SV, WH, RD>(v, s, lat, U, kappa, in, out, fstride, nrhs, o, scale, active, part, nbs)
   if (which == 0) { if (red == 0) DL_W(0, 0); else if (red == 1) DL_W(0, 1); else DL_W(0, 2); }
