@@ -187,10 +187,12 @@ void eo_merge(hipStream_t s, const Lattice& full, const double2* half, double2* 
 // out_{par} = kappa_fac * D_{par, 1-par} in_{1-par} + add_{par} (FP64 half fields; add may be NULL).
 void eo_hop_f64(hipStream_t s, const Lattice& lat, const double2* U, double kappa_fac, int par, const double2* in,
                 const double2* add, double2* out);
+// The launch shapes that differ on this lattice for nrhs right-hand sides, which the autotuner times.
+std::vector<WilsonCfg> wilson_candidates(const Lattice& lat, bool fp64, int nrhs);
 // Batched Wilson apply in FP64 (R = double) or FP32 (R = float): nrhs fields at stride fstride.
 // Partials (red != 0) are column-major [nrhs][wilson_nbs(lat)].  Returns wilson_nbs(lat) or 0.
 int wilson_nbs(const Lattice& lat, const WilsonCfg& cfg);
-// Blocks of a launch (an upper bound where several rhs share an LDS stage).
+// Blocks of a launch.
 long wilson_grid(const Lattice& lat, const WilsonCfg& cfg, bool fp64, int nrhs);
 int wilson_max_nbs(const Lattice& lat);  // partials per rhs of the widest-grid variant
 // SV: spinor storage (double2 with R = double; float2 or bf2 with R = float); arithmetic in R.

