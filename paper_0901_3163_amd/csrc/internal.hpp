@@ -152,19 +152,17 @@ void pack_links(hipStream_t s, const Lattice& lat, const double2* host_layout, d
 // ---- launchers: Wilson operator ------------------------------------------------
 // Launch shape of the stencil: variant 0-3 = one thread per site with (threads per block,
 // occupancy hint) among {(256,2), (128,2), (512,1), (256,1)}; 4-6 = one thread per (x,y,z)
-// site marching through time chunks of 4, 8, 16 slices; 7-10 = the marching form with 64
-// sites per block, links staged in LDS and shared by (rhs per block, T) = (4, 8), (4, 16),
-// (8, 8), (2, 8); 11-14 = the marching form with each slice's spinors staged in LDS (11: with
-// the x, y links too, FP32 only; T = 8, 8, 16, 8; 14 issues each hop's loads one hop ahead); order = block order (0: rhs fastest, XCD-contiguous; 1: sites
-// fastest, XCD-contiguous; 2: rhs fastest, hardware order).  Chosen by the autotuner.
+// site marching through time chunks of 4, 8, 16 slices; 12-14 = the marching form with each
+// slice's spinors staged in LDS (T = 8, 16, 8; 14 issues each hop's loads one hop ahead);
 // 15-17 = one thread per site for 2 or 4 rhs of a group (256 threads; 2 rhs with 128 threads), each
-// hop's link loaded once for the group.  18-19 = the slice-staged form with each block a box of
-// whole x rows spanning y and z (T = 8, 16), so z neighbours inside the box come from LDS too
-// (variants 12 and 13 where no box tiles the slice).  20 = one hop per wave, eight waves per 64 sites
-// (small lattices).  21-26 = boxes of whole x rows marching through T = 4, 8, 16 slices, for one (21-23) or
-// two rhs (24-26) a block.
+// hop's link loaded once for the group; 20 = one hop per wave, eight waves per 64 sites; 21-26 =
+// boxes of whole x rows marching through T = 4, 8, 16 slices, for one (21-23) or two rhs (24-26) a
+// block.  The other numbers (wilson_retired) run as 12 or 13.  order = block order (0: rhs fastest,
+// XCD-contiguous; 1: sites fastest, XCD-contiguous; 2: rhs fastest, hardware order).  Chosen by the
+// autotuner.
 constexpr int kWilsonVariants = 27;
 constexpr int kWilsonOrders = 3;
+constexpr bool wilson_retired(int v) { return (v >= 7 && v <= 11) || v == 18 || v == 19; }
 struct WilsonCfg {
   int variant = 0;
   int order = 0;

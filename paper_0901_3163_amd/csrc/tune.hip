@@ -95,7 +95,7 @@ void load_cache() {
     double us;
     std::string tag;
     if (!(is >> tag >> arch >> dims >> prec >> nrhs >> v >> o >> us) || tag != stencil_tag()) continue;
-    if (v < 0 || v >= kWilsonVariants || o < 0 || o >= kWilsonOrders) continue;
+    if (v < 0 || v >= kWilsonVariants || wilson_retired(v) || o < 0 || o >= kWilsonOrders) continue;
     std::ostringstream k;
     k << arch << ' ' << dims << ' ' << prec << ' ' << nrhs;
     g_table[k.str()] = {WilsonCfg{v, o}, us};

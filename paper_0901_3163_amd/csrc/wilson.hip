@@ -464,33 +464,6 @@ __device__ __forceinline__ HopSrc hop_src(int hh, int d, int s3, int base3, int 
   r.near = mu < 2 && r.li < (unsigned)NT && nb3 < V3;
   return r;
 }
-// Neighbour source for a block that is a box of whole x rows: Lx x by x bz sites of the
-// slice, thread tid = lx + Lx (ly + by lz).  The x neighbour is always in the box (the box
-// holds the whole periodic row); the y (z) neighbour is in it unless the site sits on the
-// box's y (z) face, or the box spans the lattice in y (z), where the periodic neighbour is
-// in the box again.  d is the neighbour's site offset, as for hop_src.
-__device__ __forceinline__ HopSrc hop_src_box(int hh, int d, int tid, int Lx, int ly, int lz, int by, int bz,
-                                              int Ly, int Lz) {
-  const int mu = hh >> 1;
-  const bool fwd = (hh & 1) == 0;
-  HopSrc r;
-  r.d = d;
-  int dl;
-  if (mu == 0) {
-    r.near = true;
-    dl = d;  // the row's own sites: lx + 1 or the periodic wrap, as in site numbering
-  } else if (mu == 1) {
-    const bool face = fwd ? ly == by - 1 : ly == 0;
-    r.near = !face || by == Ly;
-    dl = (face ? (fwd ? 1 - by : by - 1) : (fwd ? 1 : -1)) * Lx;
-  } else {
-    const bool face = fwd ? lz == bz - 1 : lz == 0;
-    r.near = !face || bz == Lz;
-    dl = (face ? (fwd ? 1 - bz : bz - 1) : (fwd ? 1 : -1)) * (Lx * by);
-  }
-  r.li = (unsigned)(tid + dl);
-  return r;
-}
 template <class SV>
 __device__ __forceinline__ SpRaw<SV> fetch_sp(const SV* __restrict__ in, int site) {
   SpRaw<SV> r;
@@ -499,48 +472,30 @@ __device__ __forceinline__ SpRaw<SV> fetch_sp(const SV* __restrict__ in, int sit
   for (int c = 0; c < 12; ++c) r.e[c] = pp[c * kTile];
   return r;
 }
-// link of hop hh: forward hops use U_mu(x), backward hops U_mu(x - mu); with LK the x and y
-// links of the block's sites come from LDS (pu: [2][9][NT])
-template <bool LK, int NT, class C>
-__device__ __forceinline__ Lk<C> fetch_link(const C* __restrict__ U, const C* pu, int hh, const HopSrc& src, int site,
-                                            int tid) {
-  const int mu = hh >> 1;
-  const bool fwd = (hh & 1) == 0;
+// link of hop hh: forward hops use U_mu(x), backward hops U_mu(x - mu)
+template <class C>
+__device__ __forceinline__ Lk<C> fetch_link(const C* __restrict__ U, int hh, const HopSrc& src, int site) {
   Lk<C> r;
-  if (LK && fwd && mu < 2) {
+  const C* up = U + lk_base((hh & 1) == 0 ? site : site + src.d, hh >> 1);
 #pragma unroll
-    for (int e = 0; e < 9; ++e) r.e[e] = pu[(mu * 9 + e) * NT + tid];
-  } else if (LK && !fwd && src.near) {
-#pragma unroll
-    for (int e = 0; e < 9; ++e) r.e[e] = pu[(mu * 9 + e) * NT + src.li];
-  } else {
-    const C* up = U + lk_base(fwd ? site : site + src.d, mu);
-#pragma unroll
-    for (int e = 0; e < 9; ++e) r.e[e] = up[e * kTile];
-  }
+  for (int e = 0; e < 9; ++e) r.e[e] = up[e * kTile];
   return r;
 }
 
 // Time-marching form with the slice staged in LDS: a block is NT consecutive (x, y, z)
 // sites of one time chunk of one rhs.  At each slice every thread writes its centre spinor
-// and its forward x and y links to LDS; the x and y neighbours (and the backward x, y links)
-// that fall inside the block's site range are then read from LDS instead of L2 (for a
-// 16 x 16 plane per block that is all of them), the z neighbours and the z, t links come
-// from memory, and the t hops are carried along t as in k_wilson_tm.  Same arithmetic and
-// order as k_wilson.
-// BOX: the block is instead a box of by x bz whole x rows (Lx by bz = NT, by | Ly, bz | Lz),
-// so the z neighbours inside the box come from LDS as well; for a 16^3 or 32^3 slice a box
-// of 4 x 4 or 4 x 2 rows leaves 1-1.5 neighbour spinors per site to memory instead of 2-2.25.
-template <class R, class SV, int WHICH, int RED, int NT, bool LK, bool PF, bool BOX = false>
+// to LDS; the x and y neighbours that fall inside the block's site range are then read from
+// there instead of L2 (for a 16 x 16 plane per block that is all of them), the z neighbours
+// and the links come from memory, and the t hops are carried along t as in k_wilson_tm.
+// Same arithmetic and order as k_wilson.
+template <class R, class SV, int WHICH, int RED, int NT, bool PF>
 __global__ void __launch_bounds__(NT)
 k_wilson_tmp(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ in,
              SV* __restrict__ out, long fstride, int nrhs, double kappa, int Lx, int Ly, int Lz,
              int Lt, long V, long Vpad, int T, int nb3, int nbs, int order, const double* __restrict__ scale,
-             const int* __restrict__ active, double* __restrict__ part, int boy, int boz) {
-  static_assert(!(LK && BOX), "the staged links cover the x and y hops only");
+             const int* __restrict__ active, double* __restrict__ part) {
   using C = typename CT<R>::type;
-  __shared__ C ps[12 * NT];               // centre spinors of the block's sites, component-major
-  __shared__ C pu[LK ? 2 * 9 * NT : 1];   // forward x and y links of the block's sites (LK)
+  __shared__ C ps[12 * NT];  // centre spinors of the block's sites, component-major
   const int lb = order == 2 ? (int)blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
   const int rhs = order == 1 ? lb / nbs : lb % nrhs;
   const int sb = order == 1 ? lb % nbs : lb / nrhs;
@@ -551,14 +506,8 @@ k_wilson_tmp(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
   const int V3 = Lx * Ly * Lz;
   const int base3 = b3 * NT;
   const int tid = (int)threadIdx.x;
-  int s3 = base3 + tid, ly = 0, lz = 0;
-  if (BOX) {
-    const int nby = Ly / boy;
-    ly = (tid / Lx) % boy;
-    lz = tid / (Lx * boy);
-    s3 = tid % Lx + Lx * ((b3 % nby) * boy + ly + Ly * ((b3 / nby) * boz + lz));
-  }
-  const bool valid = BOX || s3 < V3;
+  const int s3 = base3 + tid;
+  const bool valid = s3 < V3;
   double red = 0.0;
   if (b3 == 0 && (tc + 1) * T >= Lt) {
     for (long sp = V + tid; sp < Vpad; sp += NT) {
@@ -606,13 +555,6 @@ k_wilson_tmp(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
     if (valid) {
 #pragma unroll
       for (int c = 0; c < 12; ++c) ps[c * NT + tid] = cen[c];
-      if (LK) {
-#pragma unroll
-        for (int e = 0; e < 9; ++e) {
-          pu[e * NT + tid] = U[lk_base(site, 0) + e * kTile];
-          pu[(9 + e) * NT + tid] = U[lk_base(site, 1) + e * kTile];
-        }
-      }
     }
     __syncthreads();
     if (valid) {
@@ -627,17 +569,14 @@ k_wilson_tmp(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
       auto hop_d = [=](int hh) {
         return hh == 0 ? fx : hh == 1 ? bx : hh == 2 ? fy : hh == 3 ? by : hh == 4 ? fz : bz;
       };
-      auto src_of = [=](int hh) {
-        return BOX ? hop_src_box(hh, hop_d(hh), tid, Lx, ly, lz, boy, boz, Ly, Lz)
-                   : hop_src<NT>(hh, hop_d(hh), s3, base3, V3);
-      };
+      auto src_of = [=](int hh) { return hop_src<NT>(hh, hop_d(hh), s3, base3, V3); };
       HopSrc nsrc{};
       SpRaw<SV> nraw{};
       Lk<C> nu{};
       if (PF) {
         nsrc = src_of(0);
         if (!nsrc.near) nraw = fetch_sp(in, site + nsrc.d);
-        nu = fetch_link<LK, NT>(U, pu, 0, nsrc, site, tid);
+        nu = fetch_link(U, 0, nsrc, site);
       }
 #pragma unroll 1
       for (int hop2 = 0; hop2 < 6; ++hop2) {
@@ -654,12 +593,12 @@ k_wilson_tmp(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
           if (hop2 < 5) {
             nsrc = src_of(hop2 + 1);
             if (!nsrc.near) nraw = fetch_sp(in, site + nsrc.d);
-            nu = fetch_link<LK, NT>(U, pu, hop2 + 1, nsrc, site, tid);
+            nu = fetch_link(U, hop2 + 1, nsrc, site);
           }
         } else {
           src = src_of(hop2);
           if (!src.near) raw = fetch_sp(in, site + src.d);
-          lk = fetch_link<LK, NT>(U, pu, hop2, src, site, tid);
+          lk = fetch_link(U, hop2, src, site);
         }
         if (src.near) {
 #pragma unroll
@@ -719,149 +658,6 @@ k_wilson_tmp(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
     __shared__ double lds[NT / 64];
     const double s2 = block_sum<NT>(red, lds);
     if (threadIdx.x == 0) part[(long)rhs * nbs + sb] = s2;
-  }
-}
-
-// Multi-rhs time-marching form: a block is 64 consecutive (x, y, z) sites (one wave per
-// rhs) of one time chunk for RB right-hand sides.  At each time slice the block stages
-// the seven links its sites use from that slice (U_x, U_y, U_z at x, at x - mu for the
-// backward hops, and U_t at x) in LDS once, and all RB waves read them from there, so a
-// link leaves L2 once per RB right-hand sides instead of once per right-hand side.  The
-// t hops are carried along t as in k_wilson_tm; the arithmetic and its order are the
-// same as in k_wilson.  Logical block = (site block, rhs group).
-template <class R, class SV, int WHICH, int RED, int RB>
-__global__ void __launch_bounds__(64 * RB)
-k_wilson_tml(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ in,
-             SV* __restrict__ out, long fstride, int nrhs, double kappa, int Lx, int Ly, int Lz,
-             int Lt, long V, long Vpad, int T, int nb3, int nbs, int ngroups, int order,
-             const double* __restrict__ scale, const int* __restrict__ active, double* __restrict__ part) {
-  using C = typename CT<R>::type;
-  constexpr int kSlots = 7, kL = kSlots * 9 * 64;
-  __shared__ C lu[kL];
-  const int lb = order == 2 ? (int)blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
-  const int grp = order == 1 ? lb / nbs : lb % ngroups;
-  const int sb = order == 1 ? lb % nbs : lb / ngroups;
-  const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
-  const int rhs = grp * RB + w;
-  bool any = false;
-#pragma unroll
-  for (int q = 0; q < RB; ++q) {
-    const int r = grp * RB + q;
-    any |= r < nrhs && (!active || active[r]);
-  }
-  if (!any) return;  // uniform over the block
-  const bool on = rhs < nrhs && (!active || active[rhs]);
-  const int b3 = sb % nb3, tc = sb / nb3;
-  const int V3 = Lx * Ly * Lz;
-  const int s3 = b3 * 64 + lane;
-  const bool valid = s3 < V3;
-  if (on) {
-    in += rhs * fstride;
-    out += rhs * fstride;
-  }
-  if (on && b3 == 0 && (tc + 1) * T >= Lt) {
-    for (long sp = V + lane; sp < Vpad; sp += 64) {
-      SV* op = out + sp_base((int)sp);
-#pragma unroll
-      for (int c = 0; c < 12; ++c) sst(op + c * kTile, CT<R>::make(0, 0));
-    }
-  }
-  int x = 0, y = 0, z = 0;
-  if (valid) {
-    x = s3 % Lx;
-    y = (s3 / Lx) % Ly;
-    z = s3 / (Lx * Ly);
-  }
-  const int sy = Lx, sz = Lx * Ly;
-  const int fx = x == Lx - 1 ? 1 - Lx : 1, bx = x == 0 ? Lx - 1 : -1;
-  const int fy = y == Ly - 1 ? (1 - Ly) * sy : sy, by = y == 0 ? (Ly - 1) * sy : -sy;
-  const int fz = z == Lz - 1 ? (1 - Lz) * sz : sz, bz = z == 0 ? (Lz - 1) * sz : -sz;
-  constexpr int SF = (WHICH == 1) ? 1 : -1;
-  const int t0 = tc * T;
-  const int t1 = t0 + T < Lt ? t0 + T : Lt;
-  const R sc = (on && scale) ? (R)scale[rhs] : (R)1;
-  const R mk = (R)(-kappa);
-  const bool work = on && valid;
-  double red = 0.0;
-  C cen[12], gb[6];
-  if (work) {
-    const int tp = t0 == 0 ? Lt - 1 : t0 - 1;
-    const int sprev = tp * V3 + s3;
-    C p[12], h[6], u[9];
-    const SV* pp = in + sp_base(sprev);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) p[c] = sld(pp + c * kTile);
-    const C* up = U + lk_base(sprev, 3);
-#pragma unroll
-    for (int e = 0; e < 9; ++e) u[e] = up[e * kTile];
-    project<3, -SF>(p, h);
-    mul_half<true>(u, h, gb);
-    const SV* cp = in + sp_base(t0 * V3 + s3);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) cen[c] = sld(cp + c * kTile);
-  }
-#pragma unroll 1
-  for (int t = t0; t < t1; ++t) {
-    const int site = t * V3 + s3;
-    __syncthreads();  // the previous slice's links are no longer read
-    if (valid) {
-      // slot k: 0-2 U_mu(x), 3-5 U_mu(x - mu) for mu = x, y, z, 6 U_t(x); this thread loads
-      // components of its own lane's site
-      for (int q = w; q < kSlots * 9; q += RB) {
-        const int slot = q / 9, e = q % 9;
-        const int mu = slot < 3 ? slot : slot < 6 ? slot - 3 : 3;
-        const int ls = slot < 3 || slot == 6 ? site : site + (mu == 0 ? bx : mu == 1 ? by : bz);
-        lu[(slot * 9 + e) * 64 + lane] = U[lk_base(ls, mu) + e * kTile];
-      }
-    }
-    __syncthreads();
-    if (work) {
-      C acc[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) acc[c] = CT<R>::make(0, 0);
-#pragma unroll 1
-      for (int mu = 0; mu < 3; ++mu) {
-        const int df = mu == 0 ? fx : mu == 1 ? fy : fz;
-        const int db = mu == 0 ? bx : mu == 1 ? by : bz;
-        hop_at<SF, false>(lu + (mu * 9) * 64 + lane, 64, in, mu, site + df, acc);
-        hop_at<-SF, true>(lu + ((3 + mu) * 9) * 64 + lane, 64, in, mu, site + db, acc);
-      }
-      const int snext = (t == Lt - 1 ? 0 : t + 1) * V3 + s3;
-      C nx[12], u[9];
-      {
-        const SV* pp = in + sp_base(snext);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) nx[c] = sld(pp + c * kTile);
-#pragma unroll
-        for (int e = 0; e < 9; ++e) u[e] = lu[(6 * 9 + e) * 64 + lane];
-        C h[6], g[6];
-        project<3, SF>(nx, h);
-        mul_half<false>(u, h, g);
-        reconstruct<3, SF>(acc, g);
-        reconstruct<3, -SF>(acc, gb);
-        project<3, -SF>(cen, h);
-        mul_half<true>(u, h, gb);
-      }
-      SV* op = out + sp_base(site);
-      R sred = 0;  // this site's share of the reduction, summed in R
-#pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        const C p = cen[c];
-        C r = CT<R>::make(fma(mk, acc[c].x, p.x) * sc, fma(mk, acc[c].y, p.y) * sc);
-        if (WHICH == 2 && c >= 6) r = CT<R>::make(-r.x, -r.y);
-        sst(op + c * kTile, r);
-        if (RED == 1) sred = fma(r.x, r.x, fma(r.y, r.y, sred));
-        if (RED == 2) sred = fma(p.x, r.x, fma(p.y, r.y, sred));
-      }
-      if (RED == 1) red += (double)sred;
-      if (RED == 2) red += (double)sred * sc;
-#pragma unroll
-      for (int c = 0; c < 12; ++c) cen[c] = nx[c];
-    }
-  }
-  if (RED != 0) {
-    red = wave_sum(red);
-    if (lane == 0 && on) part[(long)rhs * nbs + sb] = red;
   }
 }
 
@@ -1352,18 +1148,19 @@ k_wilson_box(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ 
 
 // Launch-shape variants.  0-3: k_wilson with (threads per block, occupancy hint)
 // {(256,2), (128,2), (512,1), (256,1)}; 4-6: k_wilson_tm, 256 threads per block, time
-// chunks of T = 4, 8, 16 slices; 7-10: k_wilson_tml with 64 sites per block and
-// (rhs per block, T) = (4, 8), (4, 16), (8, 8), (2, 8).
+// chunks of T = 4, 8, 16 slices; 12-14: k_wilson_tmp, T = 8, 16, 8 (14 with loads one hop ahead).
 // 15-17: k_wilson_mr with (threads per block, rhs per thread) = (256, 2), (256, 4), (128, 2).
-// 18-19: k_wilson_tmp with box blocks of whole x rows (T = 8, 16); where no box tiles the
-// slice they launch variants 12 and 13.  20: k_wilson_split, 64 sites per block.
+// 20: k_wilson_split, 64 sites per block.
 // 21-26: k_wilson_box with (rhs per block, T) = (1, 4), (1, 8), (1, 16), (2, 4), (2, 8), (2, 16) (FP64: 24-26
 // are 21-23); where no box fits a slice they launch variants 4 to 6.
-static constexpr int kVariantNT[kWilsonVariants] = {256, 128, 512, 256, 256, 256, 256, 64, 64, 64, 64, 256, 256, 256, 256,
-                                                    256, 256, 128, 256, 256, 64, 256, 256, 256, 256, 256, 256};
+// The numbers 7-11, 18 and 19 launch 12 or 13: their forms (links staged in LDS for several rhs or beside
+// the spinors, an earlier box) were the fastest for 1 of 1143 keys (37 lattices from 4^3 x 8 to 34^3 x 8 and
+// 16^3 x 64, three precisions, 1 to 64 rhs), by 1.2%, and took 29% of the tuning time.
+static constexpr int kVariantNT[kWilsonVariants] = {256, 128, 512, 256, 256, 256, 256, 256, 256, 256, 256, 256, 256, 256,
+                                                    256, 256, 256, 128, 256, 256, 64, 256, 256, 256, 256, 256, 256};
 static constexpr int kVariantT[kWilsonVariants] = {0, 0, 0, 0, 4, 8, 16, 8, 16, 8, 8, 8, 8, 16, 8, 0, 0, 0, 8, 16, 0,
                                                    4, 8, 16, 4, 8, 16};
-static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 4, 4, 8, 2, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1,
+static constexpr int kVariantRT[kWilsonVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 4, 2, 1, 1, 1,
                                                     1, 1, 1, 2, 2, 2};
 constexpr int kFirstBox = 21, kBoxNT = 256;
 
@@ -1399,31 +1196,6 @@ static void launch_one(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, do
                      kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, nbs, order, scale, active, part);
 }
 
-// Box of whole x rows for k_wilson_tmp<..., BOX>: y and z extents (by, bz) with
-// Lx by bz = nt, by | Ly and bz | Lz, chosen for the fewest neighbour spinors outside the box
-// per site (2 / by for the y faces unless by = Ly, 2 / bz for the z faces unless bz = Lz; a
-// tie goes to the larger by, the longer contiguous run of sites).  False if no box fits.
-static bool tmp_box(const Lattice& lat, int nt, int* by, int* bz) {
-  const int* L = lat.L;
-  if (L[0] > nt || nt % L[0] != 0) return false;
-  const int rows = nt / L[0];
-  double best = 1e300;
-  bool found = false;
-  for (int y = 1; y <= rows; ++y) {
-    if (rows % y != 0 || L[1] % y != 0) continue;
-    const int z = rows / y;
-    if (L[2] % z != 0) continue;
-    const double cost = (y < L[1] ? 2.0 / y : 0.0) + (z < L[2] ? 2.0 / z : 0.0);
-    if (cost <= best) {
-      best = cost;
-      *by = y;
-      *bz = z;
-      found = true;
-    }
-  }
-  return found;
-}
-
 // Box of k_wilson_box: by | Ly, bz | Lz, Lx by bz <= NT, for the least work per site: neighbour spinors from
 // memory (2 / by and 2 / bz a site unless the box spans the lattice) on top of about five spinors'
 // worth of arithmetic, over the share of threads with a site.  False if no box fills half a block.
@@ -1447,12 +1219,10 @@ static bool site_box(const Lattice& lat, int* by, int* bz) {
 }
 
 // k_wilson_box needs a box, 32-bit byte offsets (the FP64 links under 4 GB) and no more blocks a field than the
-// fused reductions take; FP64 has registers for one rhs a block only, and no LDS for a slice's links
-// beside its spinors.
+// fused reductions take; FP64 has registers for one rhs a block only.
 int wilson_shape(const Lattice& lat, int v, bool fp64) {
   int by, bz;
-  if (v == 11 && fp64) return 12;
-  if ((v == 18 || v == 19) && !tmp_box(lat, kVariantNT[v], &by, &bz)) return v - 6;
+  if (wilson_retired(v)) return kVariantT[v] == 16 ? 13 : 12;
   if (v < kFirstBox) return v;
   if ((double)lat.ntiles * kTile * kLinkC * sizeof(double2) < 4294967296.0 && site_box(lat, &by, &bz) &&
       (long)(lat.L[1] / by) * (lat.L[2] / bz) * ((lat.L[3] + kVariantT[v] - 1) / kVariantT[v]) <= kMaxPartials)
@@ -1468,8 +1238,8 @@ std::vector<WilsonCfg> wilson_candidates(const Lattice& lat, bool fp64, int nrhs
   std::vector<WilsonCfg> out;
   for (int v = 0; v < kWilsonVariants; ++v) {
     if (wilson_shape(lat, v, fp64) != v || wilson_nbs(lat, WilsonCfg{v, 0}) > kMaxPartials) continue;
-    // the family's shorter chunk is the variant before (k_wilson_tm, k_wilson_tml with 4 rhs, k_wilson_tmp, k_wilson_box)
-    const bool longer = v == 5 || v == 6 || v == 8 || v == 13 || v == 19 || v == 22 || v == 23 || v == 25 || v == 26;
+    // the family's shorter chunk is the variant before
+    const bool longer = v == 5 || v == 6 || v == 13 || v == 22 || v == 23 || v == 25 || v == 26;
     if (longer && kVariantT[v - 1] >= lat.L[3]) continue;
     for (int o = 0; o < kWilsonOrders; ++o)
       if (o != 1 || nrhs > kVariantRT[v]) out.push_back(WilsonCfg{v, o});
@@ -1496,27 +1266,14 @@ static void launch_box(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, do
                      static_cast<const SV*>(nullptr), static_cast<void*>(nullptr));
 }
 
-template <class R, class SV, int WHICH, int RED, int NT, bool LK, bool PF, bool BOX = false>
+template <class R, class SV, int WHICH, int RED, int NT, bool PF>
 static void launch_tmp(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, const SV* in,
                        SV* out, long fstride, int nrhs, int order, const double* scale, const int* active,
                        double* part, int nbs, int v) {
   const int* L = lat.L;
-  int by = 0, bz = 0;
-  if (BOX) tmp_box(lat, NT, &by, &bz);
-  hipLaunchKernelGGL((k_wilson_tmp<R, SV, WHICH, RED, NT, LK, PF, BOX>), dim3(nbs * nrhs), dim3(NT), 0, s, U, in,
-                     out, fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v],
-                     tm_nb3(lat, v), nbs, order, scale, active, part, by, bz);
-}
-
-template <class R, class SV, int WHICH, int RED, int RB>
-static void launch_tml(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, const SV* in,
-                       SV* out, long fstride, int nrhs, int order, const double* scale, const int* active,
-                       double* part, int nbs, int v) {
-  const int* L = lat.L;
-  const int ngroups = (nrhs + RB - 1) / RB;
-  hipLaunchKernelGGL((k_wilson_tml<R, SV, WHICH, RED, RB>), dim3(nbs * ngroups), dim3(64 * RB), 0, s, U, in, out,
-                     fstride, nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v],
-                     tm_nb3(lat, v), nbs, ngroups, order, scale, active, part);
+  hipLaunchKernelGGL((k_wilson_tmp<R, SV, WHICH, RED, NT, PF>), dim3(nbs * nrhs), dim3(NT), 0, s, U, in, out, fstride,
+                     nrhs, kappa, L[0], L[1], L[2], L[3], lat.V, lat.ntiles * kTile, kVariantT[v], tm_nb3(lat, v), nbs,
+                     order, scale, active, part);
 }
 
 template <class R, class SV, int WHICH, int RED, int NT, int RT>
@@ -1550,31 +1307,13 @@ static void launch_variant(int variant, hipStream_t s, const Lattice& lat, const
     case 4: case 5: case 6:
       launch_tm<R, SV, WHICH, RED, 256>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
       break;
-    case 7: case 8:
-      launch_tml<R, SV, WHICH, RED, 4>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
-      break;
-    case 9:
-      launch_tml<R, SV, WHICH, RED, 8>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
-      break;
-    case 10:
-      launch_tml<R, SV, WHICH, RED, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs, variant);
-      break;
-    case 11:
-      if constexpr (sizeof(R) == 4)
-        launch_tmp<R, SV, WHICH, RED, 256, true, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale,
-                                                        active, part, nbs, variant);
-      break;
     case 12: case 13:
-      launch_tmp<R, SV, WHICH, RED, 256, false, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active,
-                                                       part, nbs, variant);
-      break;
-    case 18: case 19:
-      launch_tmp<R, SV, WHICH, RED, 256, false, false, true>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale,
-                                                             active, part, nbs, variant);
+      launch_tmp<R, SV, WHICH, RED, 256, false>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part,
+                                                nbs, variant);
       break;
     case 14:
-      launch_tmp<R, SV, WHICH, RED, 256, false, true>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active,
-                                                      part, nbs, variant);
+      launch_tmp<R, SV, WHICH, RED, 256, true>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part,
+                                               nbs, variant);
       break;
     case 15:
       launch_mr<R, SV, WHICH, RED, 256, 2>(s, lat, U, kappa, in, out, fstride, nrhs, order, scale, active, part, nbs);
