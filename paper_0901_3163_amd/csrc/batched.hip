@@ -901,7 +901,7 @@ static void true_residual(Batch& bt, const double2* B, const double2* X, double2
     {
       TimeScope ts(bt.ctx, T_WILSON64, bt.wilson_bytes(576.0, 576.0));  // reads x and b, writes r
       nbs = wilson_residual_f64(bt.s, op0->lat, op0->U.get(), op0->kappa, X, B, R, op0->lat.nc, bt.nr,
-                                bt.active.get(), bt.part.get());
+                                bt.active.get(), bt.part.get(), wilson_cfg(op0, DL_FP64, bt.nr));
     }
     hipLaunchKernelGGL(k_b_fin_store, dim3(bt.nr), dim3(kBlock), 0, bt.s, bt.part.get(), nbs, bt.st.get(),
                        (int)B_RR);
@@ -1433,7 +1433,8 @@ static int solve_batch(const std::vector<BItem>& items, const double2* B, double
                                bt.active.get());
             TimeScope ts(bt.ctx, T_WILSON64, bt.wilson_bytes(576.0, 384.0 + kSpin * sizeof(SV)));
             npr = wilson_residual_f64(s, op0->lat, op0->U.get(), op0->kappa, X, B, nullptr, op0->lat.nc, nr,
-                                      bt.active.get(), bt.part2.get(), r32, sizeof(SV) == 4 ? DL_BF16 : DL_FP32);
+                                      bt.active.get(), bt.part2.get(), wilson_cfg(op0, DL_FP64, nr), r32,
+                                      sizeof(SV) == 4 ? DL_BF16 : DL_FP32);
           } else if (bt.ml_mode == 1 && whole) {
             // the same per lattice of a multi-lattice batch, its partials re-strided to pw per rhs
             hipLaunchKernelGGL((k_b_accum_clear<SV>), dim3(G, nr), dim3(kBlock), 0, s, g, X, e, bt.st.get(),
@@ -1444,7 +1445,8 @@ static int solve_batch(const std::vector<BItem>& items, const double2* B, double
               const long off = bt.h_off[it.r0];
               double* ip = bt.ml_part.get() + (size_t)it.r0 * bt.pw;
               const int nb = wilson_residual_f64(s, op->lat, op->U.get(), op->kappa, X + off, B + off, nullptr,
-                                                 op->lat.nc, it.nr, bt.active.get() + it.r0, ip, r32 + off,
+                                                 op->lat.nc, it.nr, bt.active.get() + it.r0, ip,
+                                                 wilson_cfg(op, DL_FP64, it.nr), r32 + off,
                                                  sizeof(SV) == 4 ? DL_BF16 : DL_FP32);
               if (nb > bt.pw) fail(DL_E_INVALID, "stencil partials exceed the batch's partial stride");
               const long n = (long)it.nr * bt.pw;

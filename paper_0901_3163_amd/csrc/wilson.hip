@@ -1686,14 +1686,27 @@ void eo_hop_f64(hipStream_t s, const Lattice& lat, const double2* U, double fac,
   DL_HIP(hipGetLastError());
 }
 
+// The residual's shape: the tuned shape of the FP64 stencil if it is one of the two marching forms, which have a
+// residual epilogue, else (small grids, where other forms win by the number of their blocks) the box or, without
+// one, k_wilson_tm with the shortest chunks that the partials hold.  Fixed at chunks of 16, the box was slower than
+// k_wilson_tm where few blocks are launched (8^4, 4 rhs 59 against 54 us, 22^4, 12 rhs 685 against 533) and the
+// reverse on large batches (16^3 x 32, 64 rhs 1122 against 1283); by this rule 33, 531 and 1122.
+int wilson_residual_shape(const Lattice& lat, const WilsonCfg& fp64) {
+  int v = wilson_shape(lat, fp64.variant % kWilsonVariants, true);
+  if (v >= kFirstBox || (v >= 4 && v <= 6)) return v;
+  for (int i = 0; i < 3; ++i) {
+    v = wilson_shape(lat, kFirstBox + i, true);
+    if (wilson_nbs(lat, WilsonCfg{v, 0}) <= kMaxPartials) break;
+  }
+  return v;
+}
+
 int wilson_residual_f64(hipStream_t s, const Lattice& lat, const double2* U, double kappa, const double2* x,
                         const double2* b, double2* r, long fstride, int nrhs, const int* active, double* part,
-                        void* lo, int lo_prec) {
+                        const WilsonCfg& fp64, void* lo, int lo_prec) {
   if (lat.eo) fail(DL_E_INVALID, "the fused residual serves whole-lattice operators");
   if ((lo == nullptr) == (r == nullptr)) fail(DL_E_INVALID, "the fused residual goes to r or to lo");
-  // k_wilson_box with one rhs a block and chunks of 16 slices, in hardware block order (16^3 x 32, 64 rhs:
-  // 1283 us by k_wilson_tm, 1122 here; chunks of 4 and 8 within 1% of it); k_wilson_tm where it has no box
-  const int v = wilson_shape(lat, kFirstBox + 2, true);
+  const int v = wilson_residual_shape(lat, fp64);  // in hardware block order
   const int nbs = tm_nb3(lat, v) * tm_chunks(lat, v);
   if (nbs > kMaxPartials) fail(DL_E_INVALID, "lattice too large for fused reduction");
   if ((long)nbs * nrhs > 2147483647L) fail(DL_E_INVALID, "grid too large");

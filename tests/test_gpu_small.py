@@ -210,3 +210,23 @@ def test_even_odd_two_rhs_a_thread_bits(gpu_ctx, which):
         for i in range(len(P)):
             assert np.array_equal(got[i], op.apply_batched(w, prec, P[i:i + 1])[0])
     op.close()
+
+
+# The FP64 residual in each shape it can take (a forced shape stands for the tuned one): both marching forms
+# with each chunk length on a ragged number of slices, and shapes without a residual form.
+@pytest.mark.parametrize("variant", [4, 6, 22, 12, 20])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_reliable_updates_in_each_residual_shape(gpu_ctx, storage, variant, monkeypatch):
+    from lattice_inputs import su3_links
+    from paper_0901_3163_amd import deflan
+    dims = (8, 12, 4, 19)
+    U = su3_links(dims, 4)
+    ora = dirac.WilsonOperator(U, dims, 0.12)
+    op = deflan.Operator(gpu_ctx, dims, U, 0.12, deflan.DL_MDAGM)
+    B = np.stack([gaussian_spinor(dims, 90 + i) for i in range(3)])
+    monkeypatch.setenv("DEFLAN_WILSON_VARIANT", f"{variant},0")
+    X, st, rc = op.solve_next(B, None, 1e-10, storage={"f32": 1, "bf16": 2}[storage], batched=1, reliable_every=8)
+    assert rc == 0
+    for b, x in zip(B, X):
+        assert np.linalg.norm(b.ravel() - ora.M(x.ravel())) <= 1.0001e-10 * np.linalg.norm(b)
+    op.close()

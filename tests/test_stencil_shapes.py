@@ -24,6 +24,7 @@ int candidates(const int* d, int fp64, int nrhs, int* out) {
   }
   return n;
 }
+int residual(const int* d, int v) { return wilson_residual_shape(make_lattice(d), WilsonCfg{v, 0}); }
 }
 """
 
@@ -94,3 +95,21 @@ def test_tuner_times_every_launch_once(lib, dims, fp64, nrhs):
 
     want = {launch(v, o) for v in range(27) for o in range(3) if lib.nbs(d, v) <= 16384}
     assert len(set(cands)) == n and set(cands) == want
+
+
+@pytest.mark.parametrize("dims", BOXED + NOBOX + [(64, 64, 64, 96)])
+def test_residual_follows_the_tuned_stencil(lib, dims):
+    """The FP64 residual runs in the FP64 stencil's tuned shape where that has a residual form, else with
+    the shortest chunks, and never on more blocks than the reduction's partials hold."""
+    d = dims4(*dims)
+    box = dims in BOXED
+    for v in range(27):
+        s = lib.shape(d, v, 1)
+        got = lib.residual(d, v)
+        if s in (4, 5, 6) or s >= 21:
+            assert got == s
+        elif dims == (64, 64, 64, 96):  # links above 4 GB: no box; 16384 partials hold chunks of 8 slices
+            assert got == 5
+        else:
+            assert got == (21 if box else 4)
+        assert s == got or lib.nbs(d, got) <= 16384
