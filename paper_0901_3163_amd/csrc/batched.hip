@@ -814,9 +814,10 @@ static int bwilson_multi(Batch& bt, int mode, int which, const SV* in, SV* out, 
 // Chooses the multi-lattice stencil form at the batch's setup, outside any graph capture: the
 // per-lattice shapes (storage precision and FP64) are settled first, so that no captured
 // block tunes, then both forms of the M apply are timed on zeroed temporary fields (3 applies
-// each after a warm-up) and the faster is kept for the batch's lifetime (so the partial
-// stride a solve reads stays the same).  DEFLAN_MULTI_STENCIL=list or =lattice forces a form;
-// with autotuning off the work list is taken.
+// each after a warm-up) and the faster is remembered for the batch's lattices and rhs counts: the two forms
+// sum the fused reductions in different groups, so timing each batch anew let equal solves differ in
+// their last bits where the times are close (two small lattices: one launch of 9 us or two of 5).
+// DEFLAN_MULTI_STENCIL=list or =lattice forces a form; with autotuning off the work list is taken.
 template <class SV>
 static int ml_choose(Batch& bt) {
   constexpr int prec = sizeof(SV) == sizeof(float2) ? DL_FP32 : DL_BF16;
@@ -828,37 +829,44 @@ static int ml_choose(Batch& bt) {
   }
   if (e && std::strcmp(e, "lattice") == 0) return 1;
   if (!autotune_enabled()) return 0;
-  // two fields of bt.total SV elements, allocated as double2 (16 B) and zeroed
-  const long nd = (long)((bt.total * (long)sizeof(SV) + 15) / 16);
-  DBuf<double2> tin, tout;
-  tin.alloc((size_t)nd);
-  tout.alloc((size_t)nd);
-  zero(bt.s, nd, tin.get());
-  const SV* in = reinterpret_cast<const SV*>(tin.get());
-  SV* out = reinterpret_cast<SV*>(tout.get());
-  bt.push_active();
-  hipEvent_t a, b;
-  DL_HIP(hipEventCreate(&a));
-  DL_HIP(hipEventCreate(&b));
-  float ms[2] = {0.f, 0.f};
-  for (int m = 0; m < 2; ++m) {
-    bwilson_multi<float, SV>(bt, m, 0, in, out, 0, nullptr, nullptr);
-    DL_HIP(hipEventRecord(a, bt.s));
-    for (int rep = 0; rep < 3; ++rep) bwilson_multi<float, SV>(bt, m, 0, in, out, 0, nullptr, nullptr);
-    DL_HIP(hipEventRecord(b, bt.s));
-    DL_HIP(hipEventSynchronize(b));
-    DL_HIP(hipEventElapsedTime(&ms[m], a, b));
+  std::string batch = std::to_string(prec) + ' ';
+  for (size_t i = 0; i < bt.items.size(); ++i) {
+    const int* L = bt.items[i].op->lat.L;
+    batch += (i ? "," : "") + std::to_string(L[0]) + 'x' + std::to_string(L[1]) + 'x' + std::to_string(L[2]) + 'x' +
+             std::to_string(L[3]) + ':' + std::to_string(bt.items[i].nr);
   }
-  (void)hipEventDestroy(a);
-  (void)hipEventDestroy(b);
-  const int mode = ms[1] < ms[0] ? 1 : 0;
-  if (verbose()) {
-    std::fprintf(stderr, "[deflan] multi-lattice stencil (%d lattices, %d rhs): work list %.1f us, per-lattice tuned "
-                 "launches %.1f us -> %s\n", (int)bt.items.size(), bt.nr, 1e3 * ms[0] / 3, 1e3 * ms[1] / 3,
-                 mode ? "per lattice" : "work list");
-    std::fflush(stderr);
-  }
-  return mode;
+  return multi_form(bt.ctx->device, batch, [&](double* us) {
+    // two fields of bt.total SV elements, allocated as double2 (16 B) and zeroed
+    const long nd = (long)((bt.total * (long)sizeof(SV) + 15) / 16);
+    DBuf<double2> tin, tout;
+    tin.alloc((size_t)nd);
+    tout.alloc((size_t)nd);
+    zero(bt.s, nd, tin.get());
+    const SV* in = reinterpret_cast<const SV*>(tin.get());
+    SV* out = reinterpret_cast<SV*>(tout.get());
+    bt.push_active();
+    hipEvent_t a, b;
+    DL_HIP(hipEventCreate(&a));
+    DL_HIP(hipEventCreate(&b));
+    for (int m = 0; m < 2; ++m) {
+      bwilson_multi<float, SV>(bt, m, 0, in, out, 0, nullptr, nullptr);
+      DL_HIP(hipEventRecord(a, bt.s));
+      for (int rep = 0; rep < 3; ++rep) bwilson_multi<float, SV>(bt, m, 0, in, out, 0, nullptr, nullptr);
+      DL_HIP(hipEventRecord(b, bt.s));
+      DL_HIP(hipEventSynchronize(b));
+      float ms = 0.f;
+      DL_HIP(hipEventElapsedTime(&ms, a, b));
+      us[m] = 1e3 * ms / 3;
+    }
+    (void)hipEventDestroy(a);
+    (void)hipEventDestroy(b);
+    if (verbose()) {
+      std::fprintf(stderr, "[deflan] multi-lattice stencil (%d lattices, %d rhs): work list %.1f us, per-lattice tuned "
+                   "launches %.1f us -> %s\n", (int)bt.items.size(), bt.nr, us[0], us[1],
+                   us[1] < us[0] ? "per lattice" : "work list");
+      std::fflush(stderr);
+    }
+  });
 }
 
 // Low-precision stencil over the whole batch (FP32 arithmetic and links; spinors stored as SV:

@@ -1,6 +1,8 @@
 // Operator, eigenvector-handle and solver declarations of libdeflan.
 #pragma once
+#include <functional>
 #include <map>
+#include <string>
 #include <vector>
 
 #include "internal.hpp"
@@ -80,6 +82,9 @@ int apply_wilson(dl_op* op, int which, const double2* in, double2* out, int red 
 // unless DEFLAN_AUTOTUNE=0), and the explicit tuner.
 WilsonCfg wilson_cfg(dl_op* op, int prec, int nrhs);
 WilsonCfg tune_wilson(dl_op* op, int prec, int nrhs, int reps, double* best_us);
+// Stencil form of a multi-lattice batch (0 one work-list launch, 1 a launch per lattice): the faster by
+// time_forms, which fills the two times, remembered per batch ("<prec> <dims>:<nrhs>,...") like the launch shapes.
+int multi_form(int device, const std::string& batch, const std::function<void(double* us)>& time_forms);
 bool autotune_enabled();  // false when DEFLAN_AUTOTUNE=0
 
 // hist (may be nullptr): residual history of the solve's right-hand sides.

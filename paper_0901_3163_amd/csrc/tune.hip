@@ -13,6 +13,7 @@
 //
 //     W27 <arch> <Lx>x<Ly>x<Lz>x<Lt> <prec> <nrhs> <variant> <order> <us>  (stencil)
 //     K <arch> <kind> <n> <nv> <nw> <grid> <tile> <us>                     (contraction)
+//     M <arch> <prec> <dims>:<nrhs>,<dims>:<nrhs>,... <form> <us> <us>     (multi-lattice stencil)
 //
 // The stencil tag names the number of shapes that were compared, so a file written when there were
 // fewer is tuned again rather than believed.
@@ -39,6 +40,7 @@ namespace {
 std::mutex g_mu;
 std::map<std::string, std::pair<WilsonCfg, double>> g_table;
 std::map<std::string, std::pair<TskCfg, double>> g_tsk;
+std::map<std::string, int> g_multi;
 bool g_loaded = false;
 
 std::string cache_path() {
@@ -89,6 +91,13 @@ void load_cache() {
       std::ostringstream k;
       k << arch << ' ' << kind << ' ' << n << ' ' << nv << ' ' << nw;
       g_tsk[k.str()] = {TskCfg{grid, tile}, us};
+      continue;
+    }
+    if (line.compare(0, 2, "M ") == 0) {  // multi-lattice stencil form
+      std::string tag, prec, batch;
+      int form;
+      if ((is >> tag >> arch >> prec >> batch >> form) && (form == 0 || form == 1))
+        g_multi[arch + ' ' + prec + ' ' + batch] = form;
       continue;
     }
     int prec, nrhs, v, o;
@@ -222,6 +231,30 @@ WilsonCfg wilson_cfg(dl_op* op, int prec, int nrhs) {
   if (!found && autotune_enabled()) c = tune_wilson(op, prec, nrhs, 10, nullptr);
   op->wcfg[okey] = c;
   return c;
+}
+
+int multi_form(int device, const std::string& batch, const std::function<void(double* us)>& time_forms) {
+  const bool forced = std::getenv("DEFLAN_WILSON_VARIANT") != nullptr;  // (then the shapes are not the tuned ones)
+  std::string key;
+  if (!forced) {
+    std::lock_guard<std::mutex> g(g_mu);
+    key = arch_name(device) + ' ' + batch;
+    load_cache();
+    auto it = g_multi.find(key);
+    if (it != g_multi.end()) return it->second;
+  }
+  double us[2];
+  time_forms(us);
+  const int form = us[1] < us[0] ? 1 : 0;
+  if (forced) return form;
+  std::lock_guard<std::mutex> g(g_mu);
+  auto [it, first] = g_multi.emplace(key, form);  // (another thread may have been first)
+  if (first) {
+    std::ostringstream os;
+    os << "M " << key << ' ' << form << ' ' << us[0] << ' ' << us[1];
+    append_line(os.str());
+  }
+  return it->second;
 }
 
 // ---- contraction launch shapes ---------------------------------------------------------

@@ -171,3 +171,26 @@ def test_windowed_minres_matches_fused(gpu_ctx, c1_config, storage):
         op.solve_next(B, eig, 1e-10, storage=st_code, batched=1, minres_window=65)
     eig.close()
     op.close()
+
+
+def test_stencil_form_is_chosen_once(gpu_ctx, monkeypatch, tmp_path):
+    """The form of the multi-lattice stencil is timed for the first batch of a kind and then remembered
+    (a line of the tuning file), so equal batches run the same launches and give the same bits."""
+    from paper_0901_3163_amd import deflan
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("DEFLAN_TUNE_CACHE", str(cache))
+    monkeypatch.delenv("DEFLAN_MULTI_STENCIL", raising=False)
+    dims = [(4, 4, 2, 6), (6, 2, 4, 4)]
+    ops = [deflan.Operator(gpu_ctx, d, su3_links(d, 60), 0.12, deflan.DL_G5M) for d in dims]
+    Bs = [np.stack([gaussian_spinor(d, 400 + 10 * j + i) for i in range(2)]) for j, d in enumerate(dims)]
+    runs = []
+    for _ in range(4):
+        X, st, rc = deflan.solve_next_multi(gpu_ctx, [(o, None, B, 1e-10) for o, B in zip(ops, Bs)])
+        assert rc == deflan.DL_OK
+        runs.append(X)
+        lines = [l for l in cache.read_text().splitlines() if l.startswith("M ")]
+        assert len(lines) == 1 and "4x4x2x6:2,6x2x4x4:2" in lines[0]
+    for X in runs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(X, runs[0]))
+    for o in ops:
+        o.close()
