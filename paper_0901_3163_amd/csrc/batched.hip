@@ -639,9 +639,10 @@ struct Batch {
   int ml_blocks = 0, ml_pstride = 0;
   // multi-lattice stencil form, chosen by timing at the batch's setup (ml_choose): -1 not yet,
   // 0 one work-list launch over all lattices, 1 one launch per lattice in its tuned shape (fused
-  // reductions re-strided from ml_part to pw partials per rhs)
+  // reductions re-strided from ml_part to ml_stride partials per rhs)
   int ml_mode = -1;
-  int pw = 0;
+  int pw = 0;         // partials per rhs that part, part2 and ml_part hold
+  int ml_stride = 0;  // partials per rhs of the per-lattice form
   DBuf<double> ml_part;
   // projection over lowered eigenvectors (eig_prec DL_FP32 / DL_BF16): rA rounded for the
   // matrix-core contraction
@@ -770,13 +771,22 @@ void Batch::build_worklists() {
 }
 
 // One lattice's fused-reduction partials (nbs per rhs, column-major) into the batch layout of
-// pw partials per rhs, zero beyond nbs, so that one reduction serves every lattice.
+// `stride` partials per rhs, zero beyond nbs, so that one reduction serves every lattice.
 __global__ void k_restride_partials(const double* __restrict__ src, int nbs, int nr, double* __restrict__ dst,
-                                    int pw) {
+                                    int stride) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)nr * pw) return;
-  const int r = (int)(i / pw), sb = (int)(i % pw);
+  if (i >= (long)nr * stride) return;
+  const int r = (int)(i / stride), sb = (int)(i % stride);
   dst[i] = sb < nbs ? src[(long)r * nbs + sb] : 0.0;
+}
+
+// Lattice it's nbs partials per rhs in ml_part -> its rows of dst at the batch's stride.
+static void restride(Batch& bt, const BItem& it, int nbs, double* dst) {
+  if (nbs > bt.ml_stride) fail(DL_E_INVALID, "stencil partials exceed the batch's partial stride");
+  const long n = (long)it.nr * bt.ml_stride;
+  hipLaunchKernelGGL(k_restride_partials, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, bt.s,
+                     bt.ml_part.get() + (size_t)it.r0 * bt.pw, nbs, it.nr, dst + (size_t)it.r0 * bt.ml_stride,
+                     bt.ml_stride);
 }
 
 // The multi-lattice stencil in form `mode` (0 work list, 1 per lattice in its tuned shape); the
@@ -801,14 +811,9 @@ static int bwilson_multi(Batch& bt, int mode, int which, const SV* in, SV* out, 
     const int nbs = wilson_batched<R>(bt.s, op->lat, U, op->kappa, which, in + off, out + off, op->lat.nc, it.nr, red,
                                       scale ? scale + it.r0 : nullptr, bt.active.get() + it.r0, ip,
                                       wilson_cfg(op, prec, it.nr));
-    if (red) {
-      if (nbs > bt.pw) fail(DL_E_INVALID, "stencil partials exceed the batch's partial stride");
-      const long n = (long)it.nr * bt.pw;
-      hipLaunchKernelGGL(k_restride_partials, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, bt.s, ip, nbs, it.nr,
-                         part + (size_t)it.r0 * bt.pw, bt.pw);
-    }
+    if (red) restride(bt, it, nbs, part);
   }
-  return red ? bt.pw : 0;
+  return red ? bt.ml_stride : 0;
 }
 
 // Chooses the multi-lattice stencil form at the batch's setup, outside any graph capture: the
@@ -823,10 +828,13 @@ static int ml_choose(Batch& bt) {
   constexpr int prec = sizeof(SV) == sizeof(float2) ? DL_FP32 : DL_BF16;
   const char* e = std::getenv("DEFLAN_MULTI_STENCIL");
   if (e && std::strcmp(e, "list") == 0) return 0;
-  for (const auto& it : bt.items) {
-    (void)wilson_cfg(it.op, prec, it.nr);
-    (void)wilson_cfg(it.op, DL_FP64, it.nr);
-  }
+  // the per-lattice form's partials: as many per rhs as the widest of the launches that it will make, not
+  // the widest shape there is (one hop per wave has 2048 blocks at 16^3 x 32, the boxes 32 to 128)
+  bt.ml_stride = 0;
+  for (const auto& it : bt.items)
+    bt.ml_stride = std::max(bt.ml_stride, wilson_red_stride(it.op->lat, wilson_cfg(it.op, prec, it.nr),
+                                                            wilson_cfg(it.op, DL_FP64, it.nr)));
+  bt.ml_stride = std::min(bt.ml_stride, bt.pw);  // (a forced shape on more blocks than pw is refused at its launch)
   if (e && std::strcmp(e, "lattice") == 0) return 1;
   if (!autotune_enabled()) return 0;
   std::string batch = std::to_string(prec) + ' ';
@@ -1444,7 +1452,7 @@ static int solve_batch(const std::vector<BItem>& items, const double2* B, double
                                       bt.active.get(), bt.part2.get(), wilson_cfg(op0, DL_FP64, nr), r32,
                                       sizeof(SV) == 4 ? DL_BF16 : DL_FP32);
           } else if (bt.ml_mode == 1 && whole) {
-            // the same per lattice of a multi-lattice batch, its partials re-strided to pw per rhs
+            // the same per lattice of a multi-lattice batch, its partials re-strided
             hipLaunchKernelGGL((k_b_accum_clear<SV>), dim3(G, nr), dim3(kBlock), 0, s, g, X, e, bt.st.get(),
                                bt.active.get());
             TimeScope ts(bt.ctx, T_WILSON64, bt.wilson_bytes(576.0, 384.0 + kSpin * sizeof(SV)));
@@ -1456,12 +1464,9 @@ static int solve_batch(const std::vector<BItem>& items, const double2* B, double
                                                  op->lat.nc, it.nr, bt.active.get() + it.r0, ip,
                                                  wilson_cfg(op, DL_FP64, it.nr), r32 + off,
                                                  sizeof(SV) == 4 ? DL_BF16 : DL_FP32);
-              if (nb > bt.pw) fail(DL_E_INVALID, "stencil partials exceed the batch's partial stride");
-              const long n = (long)it.nr * bt.pw;
-              hipLaunchKernelGGL(k_restride_partials, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ip, nb,
-                                 it.nr, bt.part2.get() + (size_t)it.r0 * bt.pw, bt.pw);
+              restride(bt, it, nb, bt.part2.get());
             }
-            npr = bt.pw;
+            npr = bt.ml_stride;
           } else {
             hipLaunchKernelGGL((k_b_accum<SV>), dim3(G, nr), dim3(kBlock), 0, s, g, X, e, bt.active.get());
             true_residual(bt, B, X, R64.get(), T64.get());

@@ -192,7 +192,9 @@ std::vector<WilsonCfg> wilson_candidates(const Lattice& lat, bool fp64, int nrhs
 int wilson_nbs(const Lattice& lat, const WilsonCfg& cfg);
 // Blocks of a launch.
 long wilson_grid(const Lattice& lat, const WilsonCfg& cfg, bool fp64, int nrhs);
-int wilson_max_nbs(const Lattice& lat);  // partials per rhs of the widest-grid variant
+int wilson_max_nbs(const Lattice& lat);  // partials per rhs of the widest grid that fused reductions take
+// Partials per rhs of a batched solve's fused reductions: the stencil in shape lo, the residual beside the tuned fp64.
+int wilson_red_stride(const Lattice& lat, const WilsonCfg& lo, const WilsonCfg& fp64);
 // SV: spinor storage (double2 with R = double; float2 or bf2 with R = float); arithmetic in R.
 template <class R, class SV>
 int wilson_batched(hipStream_t s, const Lattice& lat, const cplx_t<R>* U, double kappa, int which,

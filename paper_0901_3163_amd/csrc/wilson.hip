@@ -1747,8 +1747,15 @@ long wilson_grid(const Lattice& lat, const WilsonCfg& cfg, bool fp64, int nrhs) 
 
 int wilson_max_nbs(const Lattice& lat) {
   int m = 0;
-  for (int v = 0; v < kWilsonVariants; ++v) m = std::max(m, wilson_nbs(lat, WilsonCfg{v, 0}));
+  for (int v = 0; v < kWilsonVariants; ++v) {
+    const int nbs = wilson_nbs(lat, WilsonCfg{v, 0});
+    if (nbs <= kMaxPartials) m = std::max(m, nbs);
+  }
   return m;
+}
+
+int wilson_red_stride(const Lattice& lat, const WilsonCfg& lo, const WilsonCfg& fp64) {
+  return std::max(wilson_nbs(lat, lo), wilson_nbs(lat, WilsonCfg{wilson_residual_shape(lat, fp64), 0}));
 }
 
 template <class R, class SV>

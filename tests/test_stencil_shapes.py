@@ -24,6 +24,8 @@ int candidates(const int* d, int fp64, int nrhs, int* out) {
   }
   return n;
 }
+int max_nbs(const int* d) { return wilson_max_nbs(make_lattice(d)); }
+int stride(const int* d, int lo, int fp64) { return wilson_red_stride(make_lattice(d), WilsonCfg{lo, 0}, WilsonCfg{fp64, 0}); }
 int residual(const int* d, int v) { return wilson_residual_shape(make_lattice(d), WilsonCfg{v, 0}); }
 }
 """
@@ -113,3 +115,17 @@ def test_residual_follows_the_tuned_stencil(lib, dims):
         else:
             assert got == (21 if box else 4)
         assert s == got or lib.nbs(d, got) <= 16384
+
+
+@pytest.mark.parametrize("dims", BOXED + NOBOX + [(64, 64, 64, 4), (64, 64, 64, 16), (64, 64, 64, 96)])
+def test_partials_per_right_hand_side(lib, dims):
+    """A buffer that serves every shape holds the widest grid that a fused reduction takes (16384 partials,
+    which one hop per wave passes above a million sites); a solve in chosen shapes needs only theirs."""
+    d = dims4(*dims)
+    fits = [lib.nbs(d, v) for v in range(27) if lib.nbs(d, v) <= 16384]
+    assert lib.max_nbs(d) == max(fits) <= 16384
+    for lo in range(27):
+        for hi in range(27):
+            assert lib.stride(d, lo, hi) == max(lib.nbs(d, lo), lib.nbs(d, lib.residual(d, hi)))
+    if dims == (16, 16, 16, 32):
+        assert lib.max_nbs(d) == 2048 and lib.stride(d, 26, 22) == 64
