@@ -150,25 +150,6 @@ int nblocks_for(long n) {
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_dot_partials(long n, const double2* __restrict__ a, const double2* __restrict__ b, double* __restrict__ part) {
-  double re = 0.0, im = 0.0;
-  for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
-    const double2 x = a[i], y = b[i];
-    re = fma(x.x, y.x, re);
-    re = fma(x.y, y.y, re);
-    im = fma(x.x, y.y, im);
-    im = fma(-x.y, y.x, im);
-  }
-  __shared__ double lds[kBlock / 64];
-  const double sr = block_sum<kBlock>(re, lds);
-  const double si = block_sum<kBlock>(im, lds);
-  if (threadIdx.x == 0) {
-    part[blockIdx.x] = sr;
-    part[gridDim.x + blockIdx.x] = si;
-  }
-}
-
-__global__ void __launch_bounds__(kBlock)
 k_norm2_partials(long n, const double2* __restrict__ a, double* __restrict__ part) {
   double acc = 0.0;
   for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock) {
@@ -179,13 +160,6 @@ k_norm2_partials(long n, const double2* __restrict__ a, double* __restrict__ par
   __shared__ double lds[kBlock / 64];
   const double s = block_sum<kBlock>(acc, lds);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-int dot_partials(hipStream_t s, long n, const double2* a, const double2* b, double* part) {
-  const int nb = nblocks_for(n);
-  hipLaunchKernelGGL(k_dot_partials, dim3(nb), dim3(kBlock), 0, s, n, a, b, part);
-  DL_HIP(hipGetLastError());
-  return nb;
 }
 
 int norm2_partials(hipStream_t s, long n, const double2* a, double* part) {
@@ -244,18 +218,8 @@ __global__ void k_round_bf16(long n, const double2* __restrict__ a, bf2* __restr
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     sst(b + i, make_float2((float)a[i].x, (float)a[i].y));
 }
-__global__ void k_widen_bf16(long n, const bf2* __restrict__ a, double2* __restrict__ b) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const float2 v = sld(a + i);
-    b[i] = make_double2(v.x, v.y);
-  }
-}
 void round_bf16(hipStream_t s, long n, const double2* a, bf2* b) {
   hipLaunchKernelGGL(k_round_bf16, dim3(2048), dim3(256), 0, s, n, a, b);
-  DL_HIP(hipGetLastError());
-}
-void widen_bf16(hipStream_t s, long n, const bf2* a, double2* b) {
-  hipLaunchKernelGGL(k_widen_bf16, dim3(2048), dim3(256), 0, s, n, a, b);
   DL_HIP(hipGetLastError());
 }
 

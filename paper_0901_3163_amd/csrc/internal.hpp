@@ -230,7 +230,6 @@ void wilson_multi(hipStream_t s, const WilsonItem* d_items, int nitems, int nblo
 // ---- launchers: BLAS-1 ------------------------------------------------------
 int nblocks_for(long n);  // partial count used by the streaming reductions for length n
 // partial sums
-int dot_partials(hipStream_t s, long n, const double2* a, const double2* b, double* part);  // complex, 2 per block
 int norm2_partials(hipStream_t s, long n, const double2* a, double* part);                  // 1 per block
 // Partials are stored column-major: part[col * nparts + block].
 // out[col] = sum_i part[col * nparts + i] (fixed order); grid = width blocks; last (may be NULL):
@@ -249,6 +248,5 @@ uint64_t field_hash(hipStream_t s, long n, const double2* a);
 
 // ---- the no-allocation projection (noalloc.hip) ------------------------------------
 void noalloc_init(int device);  // once per device, with the device current (context creation)
-void widen_bf16(hipStream_t s, long n, const bf2* a, double2* b);    // b = (double) a
 
 }  // namespace dl

@@ -308,11 +308,10 @@ __global__ void k_ptc_wfrag16(const float2* __restrict__ W, u32x4_n* __restrict_
   frag[t] = r;
 }
 
-template <bool NONLIN>
 __global__ void __launch_bounds__(128)
 k_ptc_layer16_mfma(const float2* __restrict__ U, const float2* __restrict__ in, float2* __restrict__ out,
                    const u32x4_n* __restrict__ frag, int Lx, int Ly, int Lz, int Lt, int V, int ntiles,
-                   long in_stride, long out_stride, const double* __restrict__ out_scale) {
+                   long in_stride, long out_stride) {
   __shared__ __align__(16) unsigned short stage[2][3 * 64 * kMixRow];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lb = xcd_block(blockIdx.x, gridDim.x);
@@ -384,7 +383,6 @@ k_ptc_layer16_mfma(const float2* __restrict__ U, const float2* __restrict__ in, 
   }
   // epilogue: lane holds rows 8q + 4g + r (q, r < 4) of the wave's three tiles: channel o = 8 (q % 2) + 4g + r,
   // real part for q < 2, imaginary part (row 16 + o) for q >= 2
-  const float sc = out_scale ? (float)out_scale[item] : 1.f;
   const int s2 = tile * 64 + w * 32 + col;
   const bool ok = s2 < V;
 #pragma unroll
@@ -395,13 +393,10 @@ k_ptc_layer16_mfma(const float2* __restrict__ U, const float2* __restrict__ in, 
       float2 z[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) z[c] = make_float2(acc[c][4 * q + r], acc[c][4 * (q + 2) + r]);
-      float gsc = sc;
-      if (NONLIN) {
-        float n2 = 0.f;
+      float n2 = 0.f;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) n2 += z[c].x * z[c].x + z[c].y * z[c].y;
-        gsc = 1.f / sqrtf(1.f + n2);
-      }
+      for (int c = 0; c < 3; ++c) n2 += z[c].x * z[c].x + z[c].y * z[c].y;
+      const float gsc = 1.f / sqrtf(1.f + n2);
 #pragma unroll
       for (int c = 0; c < 3; ++c) out[act_idx(s2, 16, o, c)] = ok ? c_scale(z[c], gsc) : make_float2(0.f, 0.f);
     }
@@ -767,9 +762,8 @@ void forward(dl_net* net, dl_op* op, int nitems, const double2* B, float2* Y, bo
     hipLaunchKernelGGL(k_ptc_wfrag16, dim3((9 * 2 * 64 + 255) / 256), dim3(256), 0, s, W + net_weight_offset(1), fr);
     const int* L = lat.L;
     const int ntiles = (int)lat.ntiles;
-    hipLaunchKernelGGL((k_ptc_layer16_mfma<true>), dim3((unsigned)ntiles * nitems), dim3(128), 0, s, U, a.a1.get(),
-                       a.a2.get(), fr, L[0], L[1], L[2], L[3], (int)lat.V, ntiles, act_len(lat, 16), act_len(lat, 16),
-                       nullptr);
+    hipLaunchKernelGGL(k_ptc_layer16_mfma, dim3((unsigned)ntiles * nitems), dim3(128), 0, s, U, a.a1.get(), a.a2.get(),
+                       fr, L[0], L[1], L[2], L[3], (int)lat.V, ntiles, act_len(lat, 16), act_len(lat, 16));
     DL_HIP(hipGetLastError());
   } else {
     launch_layer(s, lat, U, a.a1.get(), a.a2.get(), keep ? a.z2.get() : nullptr, W + net_weight_offset(1), 16, 16,

@@ -863,15 +863,20 @@ static void mr_cycle(hipStream_t s, int m, int k, double* Tb, double* c, double*
   double* cn = qv + m1;             // m1
   double* key = cn + m1;            // m
   double* jw = key + m1;            // jac_work_upto(m)
-  const bool qr_lds = mr_qr_lds(m, true) + kStaticLds <= kLdsBytes;
+  // the QR's columns fit in LDS for every order of two rows a lane, for some of three and for none of eight
+  const bool qr_lds = NR == 2 || (NR == 3 && mr_qr_lds(m, true) + kStaticLds <= kLdsBytes);
   const bool or_lds = mr_orth_lds(m, k, true) + kStaticLds <= kLdsBytes;
   const dim3 one(1), wide(kSmallThreads);
-  if (qr_lds)
-    hipLaunchKernelGGL((k_mr_qr<true, (NR < 3 ? NR : 3)>), one, wide, mr_qr_lds(m, true), s, m, Tb, c, F, big, Rr, Rc,
-                       d, qv, sv, info);
-  else
-    hipLaunchKernelGGL((k_mr_qr<false, NR>), one, wide, mr_qr_lds(m, false), s, m, Tb, c, F, big, Rr, Rc, d, qv, sv,
-                       info);
+  if constexpr (NR <= 3) {
+    if (qr_lds)
+      hipLaunchKernelGGL((k_mr_qr<true, NR>), one, wide, mr_qr_lds(m, true), s, m, Tb, c, F, big, Rr, Rc, d, qv, sv,
+                         info);
+  }
+  if constexpr (NR >= 3) {
+    if (!qr_lds)
+      hipLaunchKernelGGL((k_mr_qr<false, NR>), one, wide, mr_qr_lds(m, false), s, m, Tb, c, F, big, Rr, Rc, d, qv, sv,
+                         info);
+  }
   hipLaunchKernelGGL(k_mr_trsm<NR>, dim3(m), dim3(64), 0, s, m, F, Rr, W);   // W = W^T of T_m R^-1
   hipLaunchKernelGGL(k_mr_trsm<NR>, dim3(m), dim3(64), 0, s, m, W, Rr, A);
   jacobi(s, m, A, m, 2, Z, key, jw);
