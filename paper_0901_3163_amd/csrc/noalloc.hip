@@ -15,9 +15,9 @@
 
 namespace dl {
 
-// Partials of the dots: 2 * nv * nblocks doubles (nblocks = n / 2048 rounded up, or n / 512
-// below 1024 blocks, where 512 vectors still fit), at most kNoAllocDoubles (8 MiB).  At 16^3 x 32 (n = 1572864, 768 blocks) that covers nv <= 512, at
-// 24^3 x 48 (n = 7962624) nv <= 134.
+// Partials of the dots: 2 * nv * nblocks doubles (nblocks = n / 2048 rounded up, or n / 512 while that
+// is below 256: at most 1020, where 512 vectors still fit), at most kNoAllocDoubles (8 MiB).  At
+// 16^3 x 32 (n = 1572864, 768 blocks) that covers nv <= 512, at 24^3 x 48 (n = 7962624) nv <= 134.
 constexpr long kNoAllocDoubles = 1L << 20;
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
 

@@ -63,14 +63,14 @@ __device__ __forceinline__ void transport3(const float2 u[9], bool fwd, const fl
   }
 }
 
-// One network layer over `gridDim.y` fields: thread = site.
+// One network layer over gridDim.x / nblk fields: thread = site.
 // ACT 1: out = f(z), z saved to zsave if given;
 // 2 (backward): out = the gradient G_z behind the non-linearity, from the sum G_f and z = zsave,
 // G_z = g G_f + 2 g' Re<G_f, z> z with g(s) = (1 + s)^-1/2, s = |z|^2 (a pass over G of its own took
 // 348 us for 16 channels of 8 fields of 16^3 x 32).
 // The weights are the same for every lane, so they come through the scalar cache and are SGPR operands.
 // Bound by the vector FMAs: 8 fields of 16^3 x 32 16 -> 16 1.16 -> 0.99 ms (0.96 of it issue), 4 -> 16 0.35 -> 0.33
-// (0.29); the weights in LDS and each channel's loads waited for took the difference.
+// (0.27); the weights in LDS and each channel's loads waited for took the difference.
 template <int CIN, int COUT, int ACT>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(CIN == 4 ? 2 : 3, CIN == 4 ? 2 : 3)))
@@ -180,9 +180,10 @@ k_ptc_layer(const float2* __restrict__ U, const float2* __restrict__ in, float2*
 // meet in LDS, and each mixes them into two of the outputs (out = out_scale[item] * z; out_scale may be
 // NULL), in the same order as one thread per site would.  Bound by what misses the L2: a site is read nine
 // times, and with one site per thread an XCD's 32 CUs held 32 * 1024 sites of 384 B, three times its 4 MB,
-// so that 90 % of the reads went past it (7.4 TB/s).  Two waves per tile keep as many waves on fewer
-// sites: 16 fields of 16^3 x 32 1158 -> 870 us, of which the vector FMAs are 650 (one thread per site with
-// its loads ahead 1018, one or two such waves per SIMD 1240 and 1018; four or five blocks a CU 1000 and 1040).
+// so that 90 % of the reads went past it.  Two waves per tile keep as many waves on fewer
+// sites: 16 fields of 16^3 x 32 1158 -> 870 to 917 us, of which vector issue is 715 and where 44M of 71M requests
+// still miss (one thread per site with its loads ahead 1018, one or two such waves per SIMD 1240 and 1018;
+// four or five blocks a CU 1000 and 1040).
 __global__ void __launch_bounds__(128)
 k_ptc_layer16_4(const float2* __restrict__ U, const float2* __restrict__ in, float2* __restrict__ out,
                 const float2* __restrict__ W, int Lx, int Ly, int Lz, int Lt, int V, int ntiles, long in_stride,
@@ -269,9 +270,10 @@ k_ptc_layer16_4(const float2* __restrict__ U, const float2* __restrict__ in, flo
 // of both operands; the result register j of lane l is row 8 (j / 4) + 4 (l / 32) + j % 4, so a
 // lane holds the real and imaginary parts of 8 output channels for the 3 colours of two sites,
 // which is all the per-channel non-linearity needs.
-// Bound by the latency of the loads and the vector work of the transport (16 fields of 16^3 x 32: 0.47 ms of
+// Bound by the latency of the loads and the vector work of the transport (16 fields of 16^3 x 32: 0.48 ms of
 // issue; the products 0.05).  Two waves share a tile and the next hop's loads are in flight during the products:
-// 1509 -> 917 us.  One wave per tile with its loads ahead took 1041, with 62M L2 misses (7.7 TB/s) against 29M.
+// 1509 -> 917 to 953 us, 29M of 85M requests missing the L2.  One wave per tile with its loads ahead took 1041,
+// with twice the misses.
 typedef __bf16 bf16x8_n __attribute__((ext_vector_type(8)));
 typedef float f32x16_n __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4_n __attribute__((ext_vector_type(4)));
@@ -419,13 +421,13 @@ __global__ void k_ptc_adjoint_weights(const float2* __restrict__ W, float2* __re
 // and imaginary parts of g's channels, columns those of a's, so a lane's one LDS read per operand gives
 // a real and an imaginary row (column), and each wave takes a quarter of the 192 products.  Then
 // G = sum g conj(a) is Re = <g_re, a_re> + <g_im, a_im>, Im = <g_im, a_re> - <g_re, a_im>.  Products of
-// two FP32 numbers are exact in FP64 and summed in FP64, as before.  Bound by the FP64 matrix rate
+// two FP32 numbers are exact in FP64 and summed in FP64.  Bound by the FP64 matrix rate
 // and the vector instructions around it, which do not overlap with FP64 matrix products (16 -> 16, 8 fields of
-// 16^3 x 32: 0.74 + 0.35 ms); with vector FMAs, a conversion per operand and gathered loads it took 3.69 ms,
-// now 1.35 (16 -> 4: 2.05 -> 0.80, 4 -> 16: 1.67 -> 0.74).  The nine hops of a chunk range are neighbours on one
+// 16^3 x 32: 0.74 + 0.29 ms); with vector FMAs, a conversion per operand and gathered loads it took 3.69 ms,
+// now 1.31 (16 -> 4: 2.05 -> 0.80, 4 -> 16: 1.67 -> 0.70).  The nine hops of a chunk range are neighbours on one
 // XCD, where they read the same g and a through its L2, and the next chunk's loads are in flight during
 // the products (1.82 ms without these two).
-// part layout: part[((item * 9 + h) * COUT * CIN + p) * 2 * gridDim.x + {block (re), gridDim.x + block (im)}]
+// part layout: part[((item * 9 + h) * COUT * CIN + p) * 2 * nblk + {blk (re), nblk + blk (im)}]
 typedef double f64x4_n __attribute__((ext_vector_type(4)));
 
 template <int CIN, int COUT>

@@ -37,7 +37,7 @@ struct TskGate {
 };
 
 // Partial count tsk_dots uses for length n (partials are [2*nv][nblocks]): ceil(n / 2048), or
-// ceil(n / 512) while that is below 256 * 4.
+// ceil(n / 512) while ceil(n / 2048) is below 256.
 int tsk_nblocks(long n);
 // part <- partials of c = V^H w (sum with sum_partials(part, nb, 2*nv, c)). Returns nb.
 // with_norm: partial column 2*nv holds ||w||^2 (part needs 2*(nv+1)*nb doubles).  A closed gate

@@ -16,7 +16,8 @@
 //     M <arch> <prec> <dims>:<nrhs>,<dims>:<nrhs>,... <form> <us> <us>     (multi-lattice stencil)
 //
 // The stencil tag names the number of shapes that were compared, so a file written when there were
-// fewer is tuned again rather than believed.
+// fewer is tuned again rather than believed.  A stencil shape is timed by gamma5 M without a fused reduction; the
+// reducing forms that the solvers run follow the same choice.
 //
 // The file is $DEFLAN_TUNE_CACHE, else $HOME/.cache/deflan/tune.txt.
 // DEFLAN_AUTOTUNE=0 disables tuning (the default shapes are used).

@@ -783,8 +783,9 @@ k_wilson_mr(const typename CT<R>::type* __restrict__ U, const SV* __restrict__ i
 // the block adds the eight hops in k_wilson's order, 12 components x 64 sites over 512 threads.  What
 // bounds a small lattice is the chain of memory latencies in a thread, not bytes: k_wilson walks four
 // pairs of hops one after the other, here every load of a site is in flight at once, on eight times as
-// many waves.  FP64, one field: 4^4 8.1 -> 5.0 us, 8^4 10.3 -> 5.9 us, 8^3 x 16 9.4 -> 5.8 us.
-// On larger lattices the LDS round trip costs more than it hides and the tuner takes other shapes.
+// many waves.  FP64, one field: 4^4 8.1 -> 5.0 us, 8^4 8.2 -> 5.1 us.  The tuner takes it for one FP64 field
+// up to 16^3 x 32 (30.2 us, the box 31.2), in FP32 to 26^4, and for 12 fields to about 10^4 sites; with more
+// sites in flight the LDS round trip costs more than it hides (24^3 x 48 168 us, the box 140).
 template <int MU, int S, class C>
 __device__ __forceinline__ void add_row(int spin, const C* g0, const C* g1, C& acc) {
   // row `spin` of the rebuilt spinor from the half spinor (g0, g1), as in reconstruct()
@@ -888,13 +889,17 @@ k_wilson_split(const typename CT<R>::type* __restrict__ U, const SV* __restrict_
 // widened in LDS, so x neighbours (and y and z neighbours inside the box) are read from there, the
 // others from memory; the t hops are carried along t as in k_wilson_tm.  Every hop is unrolled
 // with its own projection, one link is loaded ahead of the hop before it, and serves the RT rhs.
-// What bounds it: FP32 instruction issue (packed FP32 arithmetic is not used), 8 hops x 108 operations
-// and the epilogue, about 1050 a site and rhs or 224 us for 64 rhs of 16^3 x 32, and below that the latency
-// of its loads: two rhs a thread halve the link loads and give two chains at two waves per SIMD.
-// 16^3 x 32, 64 BF16 rhs: 438 -> 341 us alone (2.5 TB/s algorithmic; 458 -> 374 within D-CG); 16 FP32 rhs
-// 178 -> 103 (187 -> 171 within D-CG, where its input comes from HBM); FP64, one field 35 -> 30, 64 rhs
-// 1237 -> 957; 24^3 x 48 FP64, one field 167 -> 133 (4.8 TB/s).  Without the spinors one hop ahead 64 BF16
-// rhs take 393 us.
+// What bounds it: FP32 instruction issue (packed FP32 arithmetic is not used), 8 hops x 108 operations,
+// the epilogue and the BF16 conversions, 1140 a site and rhs by the counters or 243 us for 64 rhs of
+// 16^3 x 32 (0.69 of its time), and below that the latency of its loads: two rhs a thread halve the link loads
+// and give two chains at two waves per SIMD.
+// 16^3 x 32, 64 BF16 rhs: 436 -> 352 us alone (2.4 TB/s algorithmic; 458 -> 379 within D-CG); 16 FP32 rhs
+// 178 -> 110 (187 -> 174 within D-CG, where its input comes from HBM); FP64, one field 35 -> 31, 64 rhs
+// 1237 -> 971; 24^3 x 48 FP64, one field 168 -> 140 (4.6 TB/s).  Without the spinors one hop ahead 64 BF16
+// rhs took 393 us.
+// Registers: BF16 149 (one rhs, three waves per SIMD) and 210 (two), FP32 152 to 158 (one), none spilled.  FP32 with
+// two rhs fills its 256 and spills 6 values a lane, 25 (48 B) with a fused reduction; FP64 253, with a reduction 4
+// spilled (12 B); the FP64 residual stored whole (LO 0) 20 (76 B).
 // nt: the result is stored non-temporally.  RES, LO: the residual forms of k_wilson_tm.
 template <class R, class SV, int WHICH, int RED, int RT, int NT, bool RES = false, int LO = 0>
 __global__ void __launch_bounds__(NT, RT == 1 && sizeof(R) == 4 ? 3 : 2)
@@ -1248,7 +1253,7 @@ std::vector<WilsonCfg> wilson_candidates(const Lattice& lat, bool fp64, int nrhs
 }
 
 // Inputs and results that together exceed the 256 MB Infinity Cache: storing the result past it leaves
-// the inputs there (12 FP32 rhs of 16^3 x 32 108 -> 85 us, 64 BF16 rhs 352 -> 341 us); a smaller result is
+// the inputs there (alone, 12 FP32 rhs of 16^3 x 32 108 -> 85 us, 64 BF16 rhs 352 -> 341 us); a smaller result is
 // kept for the kernel that reads it next.
 static int stream_out(long fstride, int nrhs, size_t elem) { return 2.0 * nrhs * fstride * elem > 256e6; }
 
@@ -1455,9 +1460,10 @@ __device__ __forceinline__ bool eo_group(int rg, int nrhs, const int* __restrict
 }
 
 // Both stages: bound by the latency of their loads (the links of one parity are every other site, so half
-// of each line is not used; 12 FP32 rhs of 16^3 x 32 move 1.05 GB from the caches a stage and take 21 us of
-// instruction issue).  Two rhs a thread share the link loads, each hop's loads are issued a hop ahead and
-// a site block's rhs are neighbours on one XCD: stage 1 126 -> 78 us, stage 2 139 -> 83 us.
+// of each line is not used).  Two rhs a thread share the link loads, each hop's loads are issued a hop ahead
+// and a site block's rhs are neighbours on one XCD: 12 FP32 rhs of 16^3 x 32, stage 1 126 -> 78 us, stage 2
+// 139 -> 83 us.  At three waves per SIMD (168 registers) two rhs spill in the FP32 stage 1 (3 or 19 values, 16 or
+// 24 B a lane) and one value in stage 2 with a reduction.
 // Stage 1: tmp (arithmetic precision) = D_{1-par0, par0} in for the rhs of the launch.
 template <class R, class SV, int WHICH, int RT>
 __global__ void __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2)
@@ -1690,7 +1696,7 @@ void eo_hop_f64(hipStream_t s, const Lattice& lat, const double2* U, double fac,
 // residual epilogue, else (small grids, where other forms win by the number of their blocks) the box or, without
 // one, k_wilson_tm with the shortest chunks that the partials hold.  Fixed at chunks of 16, the box was slower than
 // k_wilson_tm where few blocks are launched (8^4, 4 rhs 59 against 54 us, 22^4, 12 rhs 685 against 533) and the
-// reverse on large batches (16^3 x 32, 64 rhs 1122 against 1283); by this rule 33, 531 and 1122.
+// reverse on large batches (16^3 x 32, 64 rhs 1122 against 1283); by this rule 33, 531 and 1128.
 int wilson_residual_shape(const Lattice& lat, const WilsonCfg& fp64) {
   int v = wilson_shape(lat, fp64.variant % kWilsonVariants, true);
   if (v >= kFirstBox || (v >= 4 && v <= 6)) return v;

@@ -338,7 +338,7 @@ class Operator:
         return out
 
     def apply_batched(self, which: int, prec: int, Psi):
-        """op(psi_j) for each field of Psi ([n][V][4][3]) by the multi-rhs stencil (FP64 or FP32)."""
+        """op(psi_j) for each field of Psi ([n][V][4][3]) by the multi-rhs stencil (FP64, FP32 or BF16 storage)."""
         Psi = _c128(Psi)
         out = _empty_like(Psi, writes=12 * self.V * int(Psi.shape[0]))
         pi, mem = _ptr(Psi)
